@@ -720,7 +720,9 @@ constexpr uint32_t QWAVE = 512;              // indices per wave per step (an ei
 constexpr uint32_t PB_THREADS = 1024;        // probe block: 16 waves, one block per CU
 constexpr uint32_t PB_WAVES = PB_THREADS / 64;
 constexpr uint32_t PB_TILES = PB_WAVES * QWAVE / TILE;  // tiles one block probes per step
-constexpr uint32_t FC_WORDS = 35840;         // filter words kept in LDS (140 KiB)
+constexpr uint32_t WSTEPS = 4;               // steps per window, the unit a wave takes
+constexpr uint32_t QCAP = QWAVE;             // entries of a wave's queue
+constexpr uint32_t FC_WORDS = 35072;         // filter words kept in LDS (137 KiB)
 
 // The filter a tile is probed against: the sender's freshly built filter,
 // the caller's (plain decode), or the payload record's (receiver).
@@ -738,42 +740,40 @@ __device__ __forceinline__ RecordView query_filter(const Work &w, const QueryOut
     return rv;
 }
 
-// One filter word: from the LDS copy of the filter's first `fcw` words, else
-// from global memory (an L2 hit: the filter is small and read by every CU).
-// A lane that is not `live` (an empty queue slot) makes no memory request.
-__device__ __forceinline__ uint32_t filter_word(const uint32_t *fc, uint32_t fcw, __amdgpu_buffer_rsrc_t rs,
-                                                uint32_t wi, bool live = true) {
-    const bool in_lds = wi < fcw;
-    const uint32_t l = fc[in_lds ? wi : 0u];
-    // the offset of a word held in LDS, or of a dead lane, lies past the
-    // view: no memory access
-    const uint32_t g = buffer_u32(rs, (in_lds || !live) ? 0xfffffff0u : wi * 4u);
-    return in_lds ? l : g;
-}
-
 // Probe pass: the positives of each tile as a bitmap (pbits) and a count
 // (tcnt).  The sender already knows that its selected indices are
 // positives (S is a subset of P, Section 4), so it skips probing them.
 //
-// The random filter reads are this kernel's cost: they are L2 hits, and
-// the L2-to-CU line transfers bound it.  One 1024-thread block runs per CU
-// and keeps the first 140 KiB of the current tensor's filter in LDS, so
-// that share of the probes never leaves the CU (all of them for filters up
-// to 1,146,880 bits).  Each block owns a contiguous range of tiles, cut into
-// runs that stay inside one tensor; the LDS copy is reloaded only when a
-// run enters a new tensor.  Inside a run, waves take eighths of a tile (512
-// indices) from a shared counter, so they stay busy until the run ends.
-// The step is an eighth rather than a quarter so that the waves' survivor
-// queues leave LDS room for 20 KiB more of the filter (measured: 3% faster;
-// a sixteenth, for 9 KiB more, was slower).
+// The random filter reads that leave the CU are L2 hits, 128 bytes of L2
+// bandwidth for one bit each, and the chip serves about 266 G of them per
+// second; a random LDS read costs a CU a twelfth of that.  One 1024-thread
+// block runs per CU and keeps the first 137 KiB of the current tensor's
+// filter in LDS.  The hashes are tested in groups: an index is tested
+// against the LDS part with each hash of a group, and only if it passes is
+// one position of the group, the largest, read from memory (probe_group).
+// The group trades vector and LDS work for L2 reads (probe_hashes has the
+// rule): at share 0.31 of the filter in LDS, 0.8 reads per index instead of
+// 1.4.  The pass is then bound by vector issue (about 110 instructions per
+// 64 indices), LDS reads (70% of their rate) and L2 reads (half of theirs)
+// alike.  gfx950 issues adds, right shifts and bit operations at twice the
+// rate of multiplies, left shifts, minima and compares, which decided
+// between forms of the same arithmetic.
 //
-// Each probe round costs a wave one L2 round trip.  Once a step's
-// survivors fit in one 64-lane group (mostly positives, which take every
-// probe), the round trips, not the reads, are the cost: the next TAIL_PROBES
-// probes are then read together.  A survivor that fails the first of them
-// costs one read it did not need.
+// Each block owns a contiguous range of tiles, cut into runs that stay
+// inside one tensor; the LDS copy is reloaded only when a run enters a new
+// tensor.  Inside a run, waves take windows of up to WSTEPS steps of 512
+// indices from a shared counter.  A step's survivors of group 0 go to the
+// wave's queue, which is emptied when the next step's would not fit and at
+// the window's end: the later groups and the memory reads they leave then
+// run on full lanes, and a window pays their round trips once or twice
+// rather than every 512 indices.  The reads of one step are in flight while
+// the next step's hashes are computed.  The code is kept small (one copy of
+// the emptying loop per kind of filter): with three copies a 37 k element
+// tensor's pass took 31 us instead of 19, in instruction fetches.
+// Against testing one hash at a time over the whole step (sender's,
+// receiver's pass in us): resnet50_25m 157, 179 -> 128, 146; vgg16_138m 479,
+// 536 -> 401, 480; transformer_355m_x24 1250-1510, 2000 -> 1003, 1408.
 constexpr uint32_t RUN_TILES = 512;  // most tiles per run (LDS tile counters)
-constexpr uint32_t TAIL_PROBES = 2;  // probes per round once the survivors fit one group
 
 // The tensor totals of the probe pass: the sender's |P| and values coded,
 // the plain query's count, or the receiver's |P| (checked against the
@@ -920,11 +920,314 @@ __device__ void probe_scan(const Work &w, const QueryOut &o, uint32_t t_begin, u
     }
 }
 
+// Hashes per group, 1 to 4 and at most k.  More hashes per group trade
+// memory reads for vector work and LDS reads, so the smaller LDS's share of
+// the filter, the more pay off (sender's pass in us, standard layout):
+//   share 0.31 (25.6 M elements):    1: 161  2: 144  3: 132  4: 127
+//   share 0.54 (355 M, 24 tensors):  1: 1184 2: 1047 3: 994  4: 1105
+// An LDS share below a sixth rejects too little per hash to be worth testing
+// first (9 M elements, share 0.17: 76 us with four, 87 with one; 1 M
+// elements, 60% of them in the filter, share 0.13: 36 us with four, 33 with
+// one).  With the partitioned layout the first parts, those of the
+// first hashes, are the ones LDS holds: of three parts held (25.6 M
+// elements), groups of 2, 3 and 4 took 103, 110 and 115 us.  A filter that
+// LDS holds whole needs no memory read, and two hashes per group keep the
+// lanes of a step busy (1 M elements: 25.7 us with one, 22.8 with two).
+__device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout) {
+    uint32_t J;
+    if (lim >= m_bits)
+        J = 2u;
+    else if (layout == LAYOUT_PARTITIONED)
+        J = (uint64_t)lim * k >= 2ull * m_bits ? 2u : 1u;
+    else
+        J = 2ull * lim >= m_bits ? 3u : 6ull * lim >= m_bits ? 4u : 1u;
+    return min(J, max(k, 1u));
+}
+
+// A tensor's filter as the probe pass's waves read it: the words of the bits
+// below `lim` in LDS, with a word of all ones after them; the others through
+// a buffer view.  J hashes are a group (probe_group).
+struct ProbeFilter {
+    const uint32_t *fc;
+    const uint32_t *ps;  // part starts of a partitioned filter (LDS)
+    __amdgpu_buffer_rsrc_t bits;
+    uint32_t m_bits, k, lim, J;
+};
+
+// How a filter is read: partly from LDS in groups of several hashes
+// (standard layout), partitioned, partly from LDS one hash at a time
+// (standard, LDS holds little of it), or all from LDS (standard).
+enum ProbeKind { PK_STANDARD = 0, PK_PARTITIONED = 1, PK_SINGLE = 2, PK_LDS = 3 };
+
+// Position of hash j (key rk): in the filter, or in its part j of k.
+template <int KIND>
+__device__ __forceinline__ uint32_t probe_pos(const ProbeFilter &f, uint32_t j, uint32_t rk) {
+    const uint32_t h = mm3_seed_r(rk, j);
+    if (KIND != PK_PARTITIONED) return __umulhi(h, f.m_bits);
+    const uint32_t base = uni(f.ps[j]);
+    return base + __umulhi(h, uni(f.ps[j + 1]) - base);
+}
+
+// Bit 0: position p's bit if LDS holds it, else one.
+template <int KIND>
+__device__ __forceinline__ uint32_t lds_bit(const ProbeFilter &f, uint32_t p) {
+    return f.fc[(KIND == PK_LDS ? p : min(p, f.lim)) >> 5] >> (p & 31u);
+}
+
+// Position p's word from memory; `need` false reads nothing (an offset past
+// the view).
+__device__ __forceinline__ uint32_t mem_word(const ProbeFilter &f, uint32_t p, bool need) {
+    return buffer_u32(f.bits, need ? (p >> 5) * 4u : 0xfffffff0u);
+}
+
+// N indices (keys rk) on their way through a group of hashes: acc's bit 0
+// stays set while no bit tested in LDS is clear, top is the largest position,
+// the one read from memory if LDS does not hold it, wd the word read.
+template <uint32_t N>
+struct ProbeSet {
+    uint32_t acc[N], top[N], wd[N];
+};
+
+// Hashes [j0, j1) against the LDS part of the filter, then the memory reads,
+// all in flight before any is tested; an index that is dead, or whose
+// largest position LDS holds, reads nothing.
+template <int KIND, uint32_t N>
+__device__ __forceinline__ void probe_group(const ProbeFilter &f, uint32_t j0, uint32_t j1, const uint32_t (&rk)[N],
+                                            ProbeSet<N> &x) {
+#pragma unroll
+    for (uint32_t c = 0; c < N; ++c) x.top[c] = 0u;
+    for (uint32_t j = j0; j < j1; ++j) {
+        uint32_t p[N], wd[N];
+#pragma unroll
+        for (uint32_t c = 0; c < N; ++c) {
+            p[c] = probe_pos<KIND>(f, j, rk[c]);
+            wd[c] = f.fc[(KIND == PK_LDS ? p[c] : min(p[c], f.lim)) >> 5];
+        }
+#pragma unroll
+        for (uint32_t c = 0; c < N; ++c) {
+            if (KIND != PK_LDS) x.top[c] = max(x.top[c], p[c]);
+            x.acc[c] &= wd[c] >> (p[c] & 31u);
+        }
+    }
+    if (KIND == PK_LDS) return;
+#pragma unroll
+    for (uint32_t c = 0; c < N; ++c)
+        x.wd[c] = mem_word(f, x.top[c], ((x.acc[c] & 1u) != 0u) & (x.top[c] >= f.lim));
+}
+
+// The lanes whose index c passed the group, once its word is there.
+template <int KIND, uint32_t N>
+__device__ __forceinline__ uint64_t probe_passed(const ProbeFilter &f, const ProbeSet<N> &x, uint32_t c) {
+    if (KIND == PK_LDS) return ballot(x.acc[c] & 1u);
+    const uint64_t alive = ballot(x.acc[c] & 1u), in_lds = ballot(x.top[c] < f.lim);
+    return alive & (in_lds | ballot((x.wd[c] >> (x.top[c] & 31u)) & 1u));
+}
+
+// Appends `entry` of the lanes in mask to the queue of cnt entries.
+__device__ __forceinline__ void queue_push(uint16_t *me, uint32_t &cnt, uint64_t mask, uint32_t entry) {
+    const uint32_t at =
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, cnt));
+    if (__builtin_amdgcn_inverse_ballot_w64(mask)) me[at] = (uint16_t)entry;
+    cnt += popc64(mask);
+}
+
+// What groups 0 and 1 left of every hash, `step` (at most S) hashes of G
+// times 64 queue entries with their reads in flight together: of the first
+// two groups all but the position that was read there.  Groups of one: two
+// hashes at a time, and one while the queue is long, since an index that
+// fails the first costs the others' reads.  Returns the entries left, the
+// positives.
+template <int KIND, uint32_t G, uint32_t S>
+__device__ __forceinline__ uint32_t probe_rest(const ProbeFilter &f, uint16_t *me, uint32_t wbase, uint32_t cnt,
+                                               uint32_t step) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t tested = min(2u * f.J, f.k);
+    // where no bit of them is left, past them
+    uint32_t j0 = KIND == PK_LDS || KIND == PK_SINGLE || f.lim >= f.m_bits ? tested : 0u, n;
+    for (; j0 < f.k && cnt > 0; j0 += n) {
+        const uint32_t L = cnt;
+        n = min(S == 2 && L > 128 ? 1u : step, f.k - j0);
+        cnt = 0;
+        for (uint32_t b0 = 0; b0 < L; b0 += 64 * G) {
+            uint32_t ev[G], acc[G], p[G][S], wd[G][S];
+            bool need[G][S];
+#pragma unroll
+            for (uint32_t g = 0; g < G; ++g) {
+                const uint32_t x = b0 + g * 64 + lane;
+                ev[g] = x < L ? me[x] : 0u;
+                acc[g] = x < L ? 1u : 0u;
+                if (g > 0 && b0 + g * 64 >= L) continue;
+                const uint32_t rk = mm3_rkey(wbase + ev[g]);
+#pragma unroll
+                for (uint32_t u = 0; u < S; ++u) {
+                    p[g][u] = 0u;
+                    if (u < n) {
+                        p[g][u] = probe_pos<KIND>(f, j0 + u, rk);
+                        if (j0 + u >= tested) acc[g] &= lds_bit<KIND>(f, p[g][u]);
+                    }
+                }
+            }
+            if (KIND != PK_LDS) {
+#pragma unroll
+                for (uint32_t g = 0; g < G; ++g) {
+                    if (g > 0 && b0 + g * 64 >= L) continue;
+                    // the positions that groups 0 and 1 read
+                    uint32_t done[S];
+#pragma unroll
+                    for (uint32_t u = 0; u < S; ++u) done[u] = 0xffffffffu;
+                    if (S == 4 && j0 < tested) {
+                        const uint32_t lo = max(p[g][0], p[g][1]), hi = max(p[g][S - 2], p[g][S - 1]);
+                        done[0] = done[1] = f.J >= 3 ? max(lo, hi) : lo;
+                        done[S - 2] = done[S - 1] = f.J >= 3 ? max(lo, hi) : hi;
+                        if (KIND == PK_PARTITIONED && f.J == 1) {
+                            done[0] = p[g][0];
+                            done[1] = p[g][1];
+                            done[S - 2] = done[S - 1] = 0xffffffffu;
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t u = 0; u < S; ++u) {
+                        need[g][u] = ((acc[g] & 1u) != 0u) & (u < n) & (p[g][u] >= f.lim) & (p[g][u] != done[u]);
+                        wd[g][u] = mem_word(f, p[g][u], need[g][u]);
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (uint32_t g = 0; g < G; ++g) {
+                if (g > 0 && b0 + g * 64 >= L) continue;
+                uint64_t mask = ballot(acc[g] & 1u);
+                if (KIND != PK_LDS) {
+#pragma unroll
+                    for (uint32_t u = 0; u < S; ++u)
+                        mask &= ballot(!need[g][u] | ((wd[g][u] >> (p[g][u] & 31u)) & 1u));
+                }
+                queue_push(me, cnt, mask, ev[g]);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    return cnt;
+}
+
+// The wave's queue me[0..cnt) of indices that passed hash group 0, to its
+// positives: their bits are set in mw, the window's bitmap.
+template <int KIND>
+__device__ __forceinline__ void probe_drain(const ProbeFilter &f, uint16_t *me, uint32_t *mw, uint32_t wbase,
+                                            uint32_t cnt) {
+    const uint32_t lane = threadIdx.x & 63u;
+    constexpr uint32_t G = 4;
+    // group 1, four times 64 entries with their reads in flight together
+    if (f.J < f.k) {
+        const uint32_t L = cnt;
+        cnt = 0;
+        for (uint32_t b0 = 0; b0 < L; b0 += 64 * G) {
+            uint32_t ev[G], rk[G];
+            ProbeSet<G> y;
+#pragma unroll
+            for (uint32_t u = 0; u < G; ++u) {
+                const uint32_t x = b0 + u * 64 + lane;
+                ev[u] = x < L ? me[x] : 0u;
+                y.acc[u] = x < L ? 0xffffffffu : 0u;
+                rk[u] = mm3_rkey(wbase + ev[u]);
+            }
+            probe_group<KIND>(f, f.J, min(2u * f.J, f.k), rk, y);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (uint32_t u = 0; u < G; ++u) queue_push(me, cnt, probe_passed<KIND>(f, y, u), ev[u]);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    // what is left of every hash
+    if (KIND == PK_SINGLE)
+        cnt = probe_rest<KIND, 4, 2>(f, me, wbase, cnt, 2u);
+    else
+        cnt = probe_rest<KIND, 1, 4>(f, me, wbase, cnt, f.J == 3 ? 3u : 4u);
+    for (uint32_t x = lane; x < cnt; x += 64) {
+        const uint32_t e = me[x];
+        atomicOr(&mw[e >> 5], 1u << (e & 31u));
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The receiver's dense output starts as zeros, written while the filter reads
+// (an L2-bound loop) are in flight; the emit pass then stores only the
+// positives.  The zeros are stored non-temporally: they are not read again
+// here, and the filter's lines keep the L2 to themselves (resnet50_25m: 192
+// -> 187.5 us).
+__device__ __forceinline__ void zero_step(float *dz, uint32_t s0, uint32_t nvalid) {
+    const uint32_t lane = threadIdx.x & 63u;
+    if (s0 + QWAVE <= nvalid && ((uintptr_t)dz & 15u) == 0) {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (uint32_t u = 0; u < QWAVE / 256; ++u) __builtin_nontemporal_store(zero4, &((f4 *)(dz + s0))[u * 64 + lane]);
+    } else {
+        for (uint32_t e = lane; e < QWAVE; e += 64)
+            if (s0 + e < nvalid) dz[s0 + e] = 0.0f;
+    }
+}
+
+// One window: the indices [wbase, wbase + nvalid) in steps of QWAVE.  The
+// reads of one step are in flight while the next step's hashes are computed.
+template <int MODE, int KIND>
+__device__ __forceinline__ void probe_window(const ProbeFilter &f, uint16_t *me, uint32_t *mw, uint32_t wbase,
+                                             uint32_t nvalid, float *dz) {
+    constexpr uint32_t N = QWAVE / 64;
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t cnt = 0;
+    ProbeSet<N> cur;
+    for (uint32_t s0 = 0;; s0 += QWAVE) {
+        ProbeSet<N> nxt;
+        if (s0 < nvalid) {
+            // group 0 of the step's 512 indices, 8 per lane
+            uint32_t rk[N];
+#pragma unroll
+            for (uint32_t c = 0; c < N; ++c) {
+                rk[c] = mm3_rkey(wbase + s0 + c * 64 + lane);
+                // the sender's selection is known to be positive
+                nxt.acc[c] = MODE == Q_ENCODE ? ~(mw[(s0 + c * 64 + lane) >> 5] >> (lane & 31u)) : 1u;
+            }
+            if (s0 + QWAVE > nvalid) {
+#pragma unroll
+                for (uint32_t c = 0; c < N; ++c)
+                    if (s0 + c * 64 + lane >= nvalid) nxt.acc[c] = 0u;
+            }
+            probe_group<KIND>(f, 0, f.J, rk, nxt);
+            if (MODE == Q_DECODE) zero_step(dz, s0, nvalid);
+        }
+        uint64_t mask[N];  // the previous step's
+        uint32_t add = 0;
+        const bool have = s0 > 0 && s0 - QWAVE < nvalid;
+        if (have) {
+#pragma unroll
+            for (uint32_t c = 0; c < N; ++c) {
+                mask[c] = probe_passed<KIND>(f, cur, c);
+                add += popc64(mask[c]);
+            }
+        }
+        // the queue is emptied when the step's survivors do not fit, and at
+        // the window's end
+        const bool end = s0 > 0 && !have;
+        if (end || cnt + add > QCAP) {
+            probe_drain<KIND>(f, me, mw, wbase, cnt);
+            cnt = 0;
+        }
+        if (end) break;
+        if (have) {
+#pragma unroll
+            for (uint32_t c = 0; c < N; ++c) queue_push(me, cnt, mask[c], s0 - QWAVE + c * 64 + lane);
+            __builtin_amdgcn_wave_barrier();
+        }
+        cur = nxt;
+    }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
-    __shared__ uint32_t fc[FC_WORDS];
-    __shared__ uint16_t qe[PB_WAVES][QWAVE];
-    __shared__ uint32_t lw[PB_WAVES][QWAVE / 32];
+    __shared__ uint32_t fc[FC_WORDS + 1];
+    __shared__ uint16_t qe[PB_WAVES][QCAP];
+    __shared__ uint32_t lw[PB_WAVES][WSTEPS * QWAVE / 32];
     __shared__ uint32_t tcl[RUN_TILES];
     __shared__ uint32_t next;
     __shared__ uint32_t ps[33];  // part starts of a partitioned filter
@@ -945,20 +1248,11 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
         // a tensor the bucketed query has done: its positives bitmap is
         // written, and the pass only counts it
         const bool pre = __builtin_amdgcn_readfirstlane(td.qb) != 0u;
-        // The sender knows its own selection to be positives.  Where it is
-        // dense (an inherently sparse gradient's support, or r >= d / 8),
-        // the step reads its selection bits first and skips the filter
-        // reads of those indices (ncf_32m, 60% selected: 0.76 -> 0.45 ms);
-        // where it is sparse the extra dependency costs more than the few
-        // reads it saves (resnet50_25m 167 -> 171 us, transformer 1.25 ->
-        // 1.40 ms), and the selection bits are read beside the filter's
-        const bool dense_sel =
-            MODE == Q_ENCODE &&
-            __builtin_amdgcn_readfirstlane(td.in.r == R_NONZERO || 8ull * td.in.r >= td.in.d ? 1u : 0u) != 0u;
         __syncthreads();  // the previous run is finished with fc, tcl and next
         if (t != cached) {
             fcw = pre ? 0u : min(rv.m_bits / 32u, FC_WORDS);
             for (uint32_t x = threadIdx.x; x < fcw; x += PB_THREADS) fc[x] = rv.bits[x];
+            if (threadIdx.x == 0) fc[fcw] = 0xffffffffu;
             if (rv.layout == LAYOUT_PARTITIONED) fill_part_starts(ps, rv.m_bits, rv.k);
             cached = t;
         }
@@ -971,170 +1265,63 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
             }
         }
         __syncthreads();
-        const uint32_t m_bits = rv.m_bits, k = rv.k, d = td.in.d;
-        const __amdgpu_buffer_rsrc_t bits = buffer_view(rv.bits, m_bits / 8u);
-        // with the partitioned layout the first parts, those of the first
-        // probes, are the ones held in LDS
-        const PosMap pm{m_bits, rv.layout == LAYOUT_PARTITIONED ? ps : nullptr};
+        const uint32_t d = td.in.d, tile0 = td.in.tile0, k = uni(rv.k);
+        const bool part = uni(rv.layout) == LAYOUT_PARTITIONED;
+        const uint32_t lim = uni(fcw * 32u);
+        const uint32_t J = uni(probe_hashes(rv.m_bits, k, lim, rv.layout));
+        const ProbeFilter f{fc, ps, buffer_view(rv.bits, rv.m_bits / 8u), uni(rv.m_bits), k, lim, J};
         uint16_t *me = qe[wv];
         uint32_t *mw = lw[wv];
+        // windows of WSTEPS steps, then of two, then of one, so that the
+        // block's waves end together
+        const uint32_t n1 = min(nq, 2u * PB_WAVES), n2 = min(nq - n1, 2u * PB_WAVES);
+        const uint32_t w4 = (nq - n1 - n2) / WSTEPS, w2 = n2 / 2u;
         for (;;) {
             uint32_t qi = 0;
             if (lane == 0) qi = atomicAdd(&next, 1u);
             qi = __builtin_amdgcn_readfirstlane(qi);
-            if (qi >= nq) break;
-            const uint32_t tile = rb + qi / QPT;
-            const uint32_t wbase = (tile - td.in.tile0) * TILE + (qi % QPT) * QWAVE;  // first index
-            if (MODE == Q_DECODE) {
-                // the receiver's dense output starts as zeros here, written
-                // while the filter reads (an L2-bound loop) are in flight;
-                // the emit pass then stores only the positives.  The zeros
-                // are stored non-temporally: they are not read again here,
-                // and the filter's lines keep the L2 to themselves
-                // (resnet50_25m: 192 -> 187.5 us)
-                float *dz = o.dense_out + td.in.off + wbase;
-                if (wbase + QWAVE <= d && ((uintptr_t)dz & 15u) == 0) {
-                    typedef float f4 __attribute__((ext_vector_type(4)));
-                    const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                    for (uint32_t u = 0; u < QWAVE / 256; ++u)
-                        __builtin_nontemporal_store(zero4, &((f4 *)dz)[u * 64 + lane]);
-                } else {
-                    for (uint32_t e = lane; e < QWAVE; e += 64)
-                        if (wbase + e < d) dz[e] = 0.0f;
-                }
-            }
-            if (pre) {
-                const uint32_t pw =
-                    lane < QWAVE / 32 ? w.pbits[(uint64_t)tile * TILE_WORDS + (qi % QPT) * (QWAVE / 32) + lane] : 0u;
-                const uint32_t pc = wave_sum(__popc(pw));
-                if (lane == 0) atomicAdd(&tcl[qi / QPT], pc);
-                // the wave reconverges here, before the next step's ticket:
-                // without it the compiler merged this lane-0 branch with
-                // the ticket's (also lane 0), so that lanes 1..63 reached
-                // the ticket's readfirstlane without lane 0, read step 0
-                // from it again and again, and the pass never ended
+            if (qi >= w4 + w2 + n1) break;
+            const uint32_t ns = qi < w4 ? WSTEPS : qi < w4 + w2 ? 2u : 1u;
+            const uint32_t st = qi < w4        ? qi * WSTEPS
+                                : qi < w4 + w2 ? w4 * WSTEPS + (qi - w4) * 2u
+                                               : w4 * WSTEPS + w2 * 2u + (qi - w4 - w2);
+            const uint32_t tile = rb + st / QPT;
+            const uint32_t wbase = (tile - tile0) * TILE + (st % QPT) * QWAVE;  // first index
+            const uint64_t word0 = (uint64_t)tile * TILE_WORDS + (st % QPT) * (QWAVE / 32);
+            const uint32_t nwords = ns * (QWAVE / 32);
+            const uint32_t nvalid = wbase < d ? min(d - wbase, ns * QWAVE) : 0u;
+            uint32_t word = 0;  // the window's bitmap, a word per lane
+            if (pre) word = lane < nwords ? w.pbits[word0 + lane] : 0u;
+            if (!pre) {
+                // the sender's selection is known to be positive
+                if (MODE == Q_ENCODE) word = lane < nwords ? w.selbits[word0 + lane] : 0u;
+                mw[lane] = word;
                 __builtin_amdgcn_wave_barrier();
-                continue;
             }
-            if (lane < QWAVE / 32) mw[lane] = 0;
-            __builtin_amdgcn_wave_barrier();
-            // probe 0 over the step's 512 indices: 8 per lane, all reads
-            // in flight before any is tested
-            uint32_t cnt = 0, known = 0;
-            uint32_t wrd[QWAVE / 64], sel[QWAVE / 64];
-            if (dense_sel) {
-                // the selection bits first; no filter read for an index of
-                // the selection or past the tensor's end
-#pragma unroll
-                for (uint32_t c = 0; c < QWAVE / 64; ++c) {
-                    const uint32_t i = wbase + c * 64 + lane;
-                    sel[c] = i < d ? w.selbits[(td.in.slot + i) >> 5] : 0u;
+            float *dz = MODE == Q_DECODE ? o.dense_out + td.in.off + wbase : nullptr;
+            if (MODE == Q_DECODE && (pre || k == 0))
+                for (uint32_t s0 = 0; s0 < nvalid; s0 += QWAVE) zero_step(dz, s0, nvalid);
+            if (!pre) {
+                if (k > 0 && nvalid > 0) {
+                    if (part)
+                        probe_window<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
+                    else if (lim >= f.m_bits)
+                        probe_window<MODE, PK_LDS>(f, me, mw, wbase, nvalid, dz);
+                    else if (J == 1)
+                        probe_window<MODE, PK_SINGLE>(f, me, mw, wbase, nvalid, dz);
+                    else
+                        probe_window<MODE, PK_STANDARD>(f, me, mw, wbase, nvalid, dz);
                 }
-#pragma unroll
-                for (uint32_t c = 0; c < QWAVE / 64; ++c) {
-                    const uint32_t i = wbase + c * 64 + lane;
-                    const uint32_t p = pm(mm3_key(i), 0);
-                    const bool need = i < d && !((sel[c] >> (lane & 31u)) & 1u);
-                    const uint32_t word = filter_word(fc, fcw, bits, p >> 5, need) >> (p & 31u);
-                    wrd[c] = (i < d && k > 0) ? word : 0u;
-                }
-            } else {
-#pragma unroll
-                for (uint32_t c = 0; c < QWAVE / 64; ++c) {
-                    const uint32_t i = wbase + c * 64 + lane;
-                    const uint32_t p = pm(mm3_key(i), 0);
-                    // p < m_bits always, so the read is in bounds; i past the
-                    // tensor's end stays inside its slot and is masked below
-                    const uint32_t word = filter_word(fc, fcw, bits, p >> 5) >> (p & 31u);
-                    wrd[c] = (i < d && k > 0) ? word : 0u;
-                    if (MODE == Q_ENCODE) {
-                        const uint32_t sw = w.selbits[(td.in.slot + i) >> 5];
-                        sel[c] = i < d ? sw : 0u;
-                    }
-                }
+                word = mw[lane];
+                if (lane < nwords) w.pbits[word0 + lane] = word;
             }
-#pragma unroll
-            for (uint32_t c = 0; c < QWAVE / 64; ++c) {
-                const uint32_t e = c * 64 + lane;
-                bool in_s = false;
-                if (MODE == Q_ENCODE) in_s = (sel[c] >> (e & 31u)) & 1u;
-                const bool hit = !in_s && (wrd[c] & 1u);
-                if (MODE == Q_ENCODE) {
-                    const uint64_t sm = ballot(in_s);
-                    if (lane < 2) mw[c * 2 + lane] |= (uint32_t)(sm >> (32 * lane));
-                    known += popc64(sm);
-                }
-                const uint64_t mask = ballot(hit);
-                if (hit) me[cnt + lanes_below(mask)] = (uint16_t)e;
-                cnt += popc64(mask);
-            }
-            // probes 1..k-1 over the survivors, compacted in place in index
-            // order; four groups of 64 queue entries have their reads in
-            // flight together
-            constexpr uint32_t G = 4;
-            for (uint32_t j = 1; j < k && cnt > 0; ++j) {
-                __builtin_amdgcn_wave_barrier();
-                const uint32_t L = cnt;
-                if (L <= 64) {
-                    // survivor x in lane x; probes j .. j + S - 1 in flight together
-                    const uint32_t S = min(k - j, TAIL_PROBES);
-                    const bool act = lane < L;
-                    const uint32_t e = act ? me[lane] : 0u;
-                    const uint32_t key = mm3_key(wbase + e);
-                    uint32_t all = 1u;
-#pragma unroll
-                    for (uint32_t u = 0; u < TAIL_PROBES; ++u) {
-                        if (u < S) {
-                            const uint32_t p = pm(key, j + u);
-                            all &= filter_word(fc, fcw, bits, p >> 5, act) >> (p & 31u);
-                        }
-                    }
-                    const bool hit = act && (all & 1u);
-                    __builtin_amdgcn_wave_barrier();
-                    const uint64_t mask = ballot(hit);
-                    if (hit) me[lanes_below(mask)] = (uint16_t)e;
-                    cnt = popc64(mask);
-                    j += S - 1;
-                    continue;
-                }
-                cnt = 0;
-                for (uint32_t b0 = 0; b0 < L; b0 += 64 * G) {
-                    uint32_t ev[G], bw[G];
-#pragma unroll
-                    for (uint32_t u = 0; u < G; ++u) {
-                        const uint32_t x = b0 + u * 64 + lane;
-                        ev[u] = x < L ? me[x] : 0u;
-                        bw[u] = 0u;
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < G; ++u) {
-                        if (b0 + u * 64 >= L) break;  // this group and the ones after it are empty
-                        const bool live = b0 + u * 64 + lane < L;
-                        const uint32_t p = pm(mm3_key(wbase + ev[u]), j);
-                        const uint32_t word = filter_word(fc, fcw, bits, p >> 5, live) >> (p & 31u);
-                        bw[u] = live ? word : 0u;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (uint32_t u = 0; u < G; ++u) {
-                        if (b0 + u * 64 >= L) break;
-                        const bool hit = bw[u] & 1u;
-                        const uint64_t mask = ballot(hit);
-                        if (hit) me[cnt + lanes_below(mask)] = (uint16_t)ev[u];
-                        cnt += popc64(mask);
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            for (uint32_t x = lane; x < cnt; x += 64) {
-                const uint32_t e = me[x];
-                atomicOr(&mw[e >> 5], 1u << (e & 31u));
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (lane < QWAVE / 32) w.pbits[(uint64_t)tile * TILE_WORDS + (qi % QPT) * (QWAVE / 32) + lane] = mw[lane];
-            if (lane == 0) atomicAdd(&tcl[qi / QPT], cnt + known);
+            const uint32_t total = wave_sum(lane < nwords ? (uint32_t)__popc(word) : 0u);
+            if (lane == 0) atomicAdd(&tcl[st / QPT], total);
+            // the wave reconverges here, before the next window's ticket:
+            // without it the compiler merged this lane-0 branch with
+            // the ticket's (also lane 0), so that lanes 1..63 reached
+            // the ticket's readfirstlane without lane 0, read window 0
+            // from it again and again, and the pass never ended
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();

@@ -297,17 +297,34 @@ __device__ __forceinline__ uint32_t mm3_key(uint32_t i) {
     return k * 0x1b873593u;
 }
 
-__device__ __forceinline__ uint32_t mm3_seed(uint32_t kmix, uint32_t seed) {
-    uint32_t h = seed ^ kmix;
-    h = rotl32(h, 13);
-    h = h * 5u + 0xe6546b64u;
-    h ^= 4u;  // input length in bytes
+__device__ __forceinline__ uint32_t mm3_mix(uint32_t h) {
+    // the input length in bytes (4), and the first shift; gfx950 issues a
+    // right shift and a three-input bit operation at twice the rate of the
+    // sub-dword exclusive or that the compiler picks for h ^ (h >> 16)
+#ifdef __HIP_DEVICE_COMPILE__
+    const uint32_t hs = h >> 16;
+    asm("v_bitop3_b32 %0, %1, %2, 4 bitop3:0x96" : "=v"(h) : "v"(h), "v"(hs));
+#else
+    h ^= 4u;
     h ^= h >> 16;
+#endif
     h *= 0x85ebca6bu;
     h ^= h >> 13;
     h *= 0xc2b2ae35u;
     h ^= h >> 16;
     return h;
+}
+
+__device__ __forceinline__ uint32_t mm3_seed(uint32_t kmix, uint32_t seed) {
+    return mm3_mix(rotl32(seed ^ kmix, 13) * 5u + 0xe6546b64u);
+}
+
+// The same from a key mix already rotated by 13 (rotation and xor commute),
+// which an index's hashes share.
+__device__ __forceinline__ uint32_t mm3_rkey(uint32_t i) { return rotl32(mm3_key(i), 13); }
+
+__device__ __forceinline__ uint32_t mm3_seed_r(uint32_t rk, uint32_t seed) {
+    return mm3_mix((rk ^ rotl32(seed, 13)) * 5u + 0xe6546b64u);
 }
 
 // Bit position of hash j for a key mix in an m-bit filter: floor(h m / 2^32).

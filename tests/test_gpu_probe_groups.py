@@ -1,0 +1,56 @@
+"""The full-range query over the forms its hash groups take: filters that the
+LDS copy holds whole, to the last word, or in part, one to thirteen hashes,
+ragged windows, and filters so full that the survivor queues overflow.  Bit-exact
+against the oracle's query."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2102_03112_amd import binding as B
+from _gpu_util import check_roundtrip, dev_tensor, host, log, run_roundtrip, sync, u64_scalar, workspace
+
+pytestmark = pytest.mark.gpu
+
+LDS_BITS = 35072 * 32  # the filter bits that the probe pass keeps in LDS
+
+# (m bits, k, share of set bits, d)
+FILTERS = [
+    (32, 1, 0.5, 1), (96, 3, 0.5, 4097), (4096, 2, 0.9, 2048), (40_000, 10, 0.5, 36_864),
+    (LDS_BITS, 10, 0.5, 70_001), (LDS_BITS + 32, 10, 0.5, 70_001), (LDS_BITS + 32, 3, 0.5, 20_481),
+    (LDS_BITS * 2, 10, 0.5, 100_003), (LDS_BITS * 2 + 32, 7, 0.5, 100_003), (LDS_BITS * 3, 1, 0.5, 9000),
+    (LDS_BITS * 3, 5, 0.97, 50_000), (LDS_BITS * 6, 13, 0.6, 33_000), (LDS_BITS * 6 + 32, 13, 0.6, 33_000),
+    (LDS_BITS * 9, 2, 0.98, 12_289), (LDS_BITS * 2, 13, 1.0, 8193), (LDS_BITS * 9, 13, 1.0, 8193),
+    (LDS_BITS, 13, 1.0, 8193),
+]
+
+
+@pytest.mark.parametrize("m,k,fill,d", FILTERS)
+def test_query_of_any_filter(m, k, fill, d):
+    import torch
+
+    log(f"query m={m} k={k} fill={fill} d={d}")
+    rng = np.random.default_rng(m + k + d)
+    words = np.packbits(rng.random(m) < fill, bitorder="little").view("<u4")
+    ref = oracle.bloom_query(words, m, k, d)
+    idx = torch.full((d,), -1, dtype=torch.int32, device="cuda")
+    n = u64_scalar()
+    B.bloom_decode(dev_tensor(words.view(np.int32)), m, k, d, idx, d, n, workspace(d))
+    sync()
+    assert int(host(n)[0]) == ref.size
+    np.testing.assert_array_equal(host(idx)[: ref.size].view(np.uint32), ref)
+
+
+# (d, ratio, fpr, layout): both directions, with the sender's own selection
+TRIPS = [
+    (300_000, (1, 4), 1e-3, 0), (300_000, (1, 2), 1e-2, 0), (300_000, (1, 4), 1e-3, 1), (300_000, (1, 8), 1e-3, 1),
+    (300_000, (1, 3), 0.3, 1), (70_000, (1, 2), 1e-4, 1), (1_200_000, (1, 2), 1e-3, 0),
+]
+
+
+@pytest.mark.parametrize("d,ratio,fpr,layout", TRIPS)
+def test_round_trip_with_large_filters(d, ratio, fpr, layout):
+    log(f"round trip d={d} ratio={ratio} fpr={fpr} layout={layout}")
+    g = (np.random.default_rng(d).standard_normal(d) * 1e-3).astype(np.float32)
+    cfg = B.Config([0, d], ratio, fpr, 3, 4, filter_layout=layout)
+    refs = oracle.roundtrip(g, [0, d], ratio, fpr, 3, 4, layout=layout)
+    check_roundtrip(g, cfg, run_roundtrip(g, cfg), refs)
