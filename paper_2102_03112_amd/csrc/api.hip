@@ -595,6 +595,32 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     return DR_OK;
 }
 
+// The words in which the call's descriptors differ from the first, grouped
+// into columns of equal differences.
+void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t> &src) {
+    a.base = t[0];
+    const uint32_t *base = (const uint32_t *)&a.base;
+    for (uint32_t i = 0; i < TINIT_WORDS; ++i) {
+        a.col[i] = INIT_SAME;
+        bool same = true;
+        for (size_t c = 1; c < t.size() && same; ++c) same = ((const uint32_t *)&t[c])[i] == base[i];
+        if (same) continue;
+        for (size_t k = 0; k < src.size() && a.col[i] == INIT_SAME; ++k) {
+            bool alike = true;
+            for (size_t c = 1; c < t.size() && alike; ++c) {
+                const uint32_t *w = (const uint32_t *)&t[c];
+                alike = w[i] - base[i] == w[src[k]] - base[src[k]];
+            }
+            if (alike) a.col[i] = (uint8_t)k;
+        }
+        if (a.col[i] == INIT_SAME) {
+            a.col[i] = (uint8_t)src.size();
+            src.push_back(i);
+        }
+    }
+    a.ncols = (uint32_t)src.size();
+}
+
 // Descriptors and the zeroed regions; a query-only work has no histogram or
 // sort regions, and `extra` (words) is a caller's buffer to clear as well.
 hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, bool query_only = false,
@@ -611,17 +637,39 @@ hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, b
                                   (uint64_t)FCNT_COPIES * FCNT_W * w.ntensors};
     }
     if (extra.p && extra.words) z.z[z.n++] = extra;
-    for (size_t f = 0; f < t.size(); f += INIT_CHUNK) {
-        InitArgs a;
-        memset(&a, 0, sizeof a);
+    InitArgs a;
+    memset(&a, 0, sizeof a);
+    std::vector<uint32_t> src;  // the descriptor word that each column follows
+    init_columns(t, a, src);
+    const size_t per = a.ncols ? INIT_DATA / a.ncols : t.size();
+    const uint32_t *base = (const uint32_t *)&a.base;
+    for (size_t f = 0; f < t.size(); f += per) {
         a.first = (uint32_t)f;
-        a.count = (uint32_t)std::min<size_t>(INIT_CHUNK, t.size() - f);
-        for (uint32_t i = 0; i < a.count; ++i) a.t[i] = t[f + i];
+        a.count = (uint32_t)std::min<size_t>(per, t.size() - f);
+        uint32_t *p = a.data;
+        for (uint32_t c = 0; c < a.count; ++c)
+            for (uint32_t i : src) *p++ = ((const uint32_t *)&t[f + c])[i] - base[i];
         hipError_t e = launch_init(w, a, z, s);
         if (e != hipSuccess) return e;
         z.n = 0;  // cleared once
     }
     return hipSuccess;
+}
+
+// What a receiver's kernels use of a tensor's plan (the rest comes from its
+// record): fewer columns, so fewer set-up launches.
+TInit receiver_init(const TInit &in) {
+    TInit r;
+    memset(&r, 0, sizeof r);
+    r.off = in.off;
+    r.slot = in.slot;
+    r.rec = in.rec;
+    r.rec_cap = in.rec_cap;
+    r.d = in.d;
+    r.tile0 = in.tile0;
+    r.ntiles = in.ntiles;
+    r.seg_slot = NO_SEG_SLOT;
+    return r;
 }
 
 bool ws_ok(void *ws, size_t ws_bytes, size_t need) {
@@ -651,6 +699,11 @@ dr_status encode_prepare(const float *g, const dr_config *cfg, uint8_t *payload,
         e.p.t[t].bits = (uint32_t *)(payload + e.rec_off[t] + HDR_BYTES);
         e.p.t[t].coef = nullptr;
         e.p.t[t].sigma = nullptr;
+        if (e.p.direct) {  // the bucketed insert's layout is not used: fewer set-up columns
+            TInit &in = e.p.t[t];
+            in.bl_pos0 = in.bl_tab0 = in.bl_poscap = 0;
+            in.bl_chunk = in.bl_chunk0 = in.bl_nchunks = in.bl_slice0 = 0;
+        }
     }
     e.w = e.p.carve.view((uint8_t *)ws);
     e.w.counts_out = counts_out;
@@ -723,7 +776,7 @@ dr_status decode_prepare(const uint8_t *payload, const dr_config *cfg, float *de
         dd.p.t[t].rec_off = dd.rec_off[t];
         dd.p.t[t].rec_cap = dd.rec_off[t + 1] - dd.rec_off[t];
         dd.p.t[t].rec = const_cast<uint8_t *>(payload) + dd.rec_off[t];
-        dd.p.t[t].bits = nullptr;
+        dd.p.t[t] = receiver_init(dd.p.t[t]);
     }
     dd.w = dd.p.carve.view((uint8_t *)ws);
     dd.dense_out = dense_out;
@@ -751,8 +804,9 @@ Carve query_carve(const Plan &p, bool with_qb = true) {
     return c;
 }
 
-dr_status decode_init(Decode &dd, bool query_only, hipStream_t s) {
-    DR_HIP(run_init(dd.w, dd.p.t, s, query_only));
+// (the receiver has no use for the histograms and the sort's counters)
+dr_status decode_init(Decode &dd, hipStream_t s) {
+    DR_HIP(run_init(dd.w, dd.p.t, s, true));
     return DR_OK;
 }
 
@@ -762,8 +816,8 @@ dr_status decode_probe(Decode &dd, uint32_t max_probe_blocks, hipStream_t s) {
     return DR_OK;
 }
 
-dr_status decode_front(Decode &dd, uint32_t max_probe_blocks, bool query_only, hipStream_t s) {
-    dr_status st = decode_init(dd, query_only, s);
+dr_status decode_front(Decode &dd, uint32_t max_probe_blocks, hipStream_t s) {
+    dr_status st = decode_init(dd, s);
     if (st != DR_OK) return st;
     return decode_probe(dd, max_probe_blocks, s);
 }
@@ -779,7 +833,7 @@ dr_status decode_impl(const uint8_t *payload, const dr_config *cfg, float *dense
     dr_status st = decode_prepare(payload, cfg, dense_out, idx_out, val_out, counts_out, ws, ws_bytes, dd);
     if (st != DR_OK) return st;
     trace_call(s);
-    st = decode_front(dd, 0xffffffffu, false, s);
+    st = decode_front(dd, 0xffffffffu, s);
     if (st != DR_OK) return st;
     return decode_back(dd, s);
 }
@@ -853,7 +907,7 @@ dr_status roundtrip_impl(const float *g, const dr_config *cfg, uint8_t *payload,
         DR_HIP(hipEventRecord(ss->start, s));
         DR_HIP(hipStreamWaitEvent(ss->s, ss->start, 0));
         trace_call(ss->s);  // per-kernel timing: the side stream's kernels count from here
-        st = decode_init(dd, true, ss->s);
+        st = decode_init(dd, ss->s);
         if (st != DR_OK) return st;
     }
     // the fork: once the sender's probe pass has written the records'
@@ -864,7 +918,7 @@ dr_status roundtrip_impl(const float *g, const dr_config *cfg, uint8_t *payload,
     if (!overlap) {
         st = encode_back(e, s);
         if (st != DR_OK) return st;
-        st = decode_front(dd, 0xffffffffu, false, s);
+        st = decode_front(dd, 0xffffffffu, s);
         if (st != DR_OK) return st;
         return decode_back(dd, s);
     }
@@ -951,7 +1005,7 @@ dr_status roundtrip_static_impl(const float *g, const dr_config *cfg, uint8_t *p
     if (st != DR_OK) return st;
     st = encode_back(e, s);
     if (st != DR_OK) return st;
-    st = decode_front(dd, 0xffffffffu, false, s);
+    st = decode_front(dd, 0xffffffffu, s);
     if (st != DR_OK) return st;
     return decode_back(dd, s);
 }
@@ -982,8 +1036,7 @@ dr_status decode_sum_impl(const uint8_t *const *payloads, uint32_t npay, const d
             in.rec_off = rec_off[t];
             in.rec_cap = rec_off[t + 1] - rec_off[t];
             in.rec = const_cast<uint8_t *>(payloads[q]) + rec_off[t];
-            in.bits = nullptr;
-            vt.push_back(in);
+            vt.push_back(receiver_init(in));
         }
     Carve c;
     c.query_only = true;

@@ -15,29 +15,49 @@
 //      ties at the threshold by index order.
 // The support of an inherently sparse gradient (Section 3) is the bitmap of
 // nonzeros, written by the same pass.
+#include <stddef.h>
+
 #include "launch.hpp"
 
 namespace dr {
 
-// Set-up: block 0 writes the tensor descriptors of this chunk (the
-// device-produced fields start at zero); every block clears its share of
-// the zero ranges.
+// Word i of the descriptor of the launch's tensor c.
+__device__ __forceinline__ uint32_t init_word(const InitArgs &a, uint32_t c, uint32_t i) {
+    const uint32_t k = a.col[i];
+    return ((const uint32_t *)&a.base)[i] + (k == INIT_SAME ? 0u : a.data[c * a.ncols + k]);
+}
+
+// Set-up: the blocks write the tensor descriptors of this launch, a word per
+// thread (the device-produced fields start at zero), and the tile table, and
+// clear their shares of the zero ranges.
 __global__ __launch_bounds__(NTHREADS) void k_init(Work w, InitArgs a, ZeroArgs z) {
-    if (blockIdx.x == 0 && threadIdx.x < a.count) {
-        TDesc &t = w.td[a.first + threadIdx.x];
-        uint32_t *dev = (uint32_t *)&t + sizeof(TInit) / 4;
-        for (uint32_t q = 0; q < (sizeof(TDesc) - sizeof(TInit)) / 4; ++q) dev[q] = 0u;
-        t.in = a.t[threadIdx.x];
-        // known before any data is seen: |S| = r for top-r, and a filter size
-        // given by the caller or computed on the host from r
-        if (t.in.r != R_NONZERO) t.n = t.in.r;
-        t.m_words = t.in.m_words_in;
-    }
+    constexpr uint32_t DW = sizeof(TDesc) / 4;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint32_t c = 0; c < a.count; ++c) {
-        const TInit &in = a.t[c];
-        for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < in.ntiles; i += stride)
-            w.tile_tensor[in.tile0 + i] = a.first + c;
+    const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    for (uint64_t q = t0; q < (uint64_t)a.count * DW; q += stride) {
+        const uint32_t c = (uint32_t)(q / DW), i = (uint32_t)(q % DW);
+        uint32_t v = 0;
+        if (i < TINIT_WORDS) {
+            v = init_word(a, c, i);
+        } else if (i == offsetof(TDesc, n) / 4) {
+            // known before any data is seen: |S| = r for top-r, and a filter
+            // size given by the caller or computed on the host from r
+            v = init_word(a, c, offsetof(TInit, r) / 4);
+            if (v == R_NONZERO) v = 0;
+        } else if (i == offsetof(TDesc, m_words) / 4) {
+            v = init_word(a, c, offsetof(TInit, m_words_in) / 4);
+        }
+        ((uint32_t *)&w.td[a.first + c])[i] = v;
+    }
+    // the waves share out the tensors, and several waves a tensor's tiles
+    // where there are more waves than tensors
+    const uint32_t nw = gridDim.x * NWAVES, parts = max(1u, nw / max(1u, a.count));
+    for (uint32_t q = __builtin_amdgcn_readfirstlane((uint32_t)(t0 >> 6)); q < a.count * parts; q += nw) {
+        const uint32_t c = q % a.count;
+        const uint32_t tile0 = init_word(a, c, offsetof(TInit, tile0) / 4);
+        const uint32_t ntiles = init_word(a, c, offsetof(TInit, ntiles) / 4);
+        for (uint64_t i = (uint64_t)(q / a.count) * 64 + (threadIdx.x & 63u); i < ntiles; i += (uint64_t)parts * 64)
+            w.tile_tensor[tile0 + i] = a.first + c;
     }
     for (uint32_t r = 0; r < z.n; ++r) {
         uint32_t *p = (uint32_t *)z.z[r].p;
@@ -48,6 +68,7 @@ __global__ __launch_bounds__(NTHREADS) void k_init(Work w, InitArgs a, ZeroArgs 
 hipError_t launch_init(const Work &w, const InitArgs &a, const ZeroArgs &z, hipStream_t s) {
     uint64_t words = 0;
     for (uint32_t r = 0; r < z.n; ++r) words += z.z[r].words;
+    words += (uint64_t)a.count * (sizeof(TDesc) / 4);
     const uint64_t blocks = words / (NTHREADS * 8) + 1;
     k_init<<<blocks < 1024 ? (uint32_t)blocks : 1024u, NTHREADS, 0, s>>>(w, a, z);
     trace_mark(s, "k_init");
