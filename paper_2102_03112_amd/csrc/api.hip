@@ -621,6 +621,13 @@ void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t
     a.ncols = (uint32_t)src.size();
 }
 
+// Tensors of fewer tiles than a 256th of all, a probe block's share.
+uint32_t tiny_tensors(const std::vector<TInit> &t, uint64_t ntiles) {
+    uint32_t n = 0;
+    for (const TInit &in : t) n += in.ntiles < ceil_div(ntiles, 256) ? 1u : 0u;
+    return n;
+}
+
 // Descriptors and the zeroed regions; a query-only work has no histogram or
 // sort regions, and `extra` (words) is a caller's buffer to clear as well.
 hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, bool query_only = false,
@@ -707,6 +714,7 @@ dr_status encode_prepare(const float *g, const dr_config *cfg, uint8_t *payload,
     }
     e.w = e.p.carve.view((uint8_t *)ws);
     e.w.counts_out = counts_out;
+    e.w.tiny = tiny_tensors(e.p.t, e.p.carve.ntiles);
     return DR_OK;
 }
 
@@ -779,6 +787,7 @@ dr_status decode_prepare(const uint8_t *payload, const dr_config *cfg, float *de
         dd.p.t[t] = receiver_init(dd.p.t[t]);
     }
     dd.w = dd.p.carve.view((uint8_t *)ws);
+    dd.w.tiny = tiny_tensors(dd.p.t, dd.p.carve.ntiles);
     dd.dense_out = dense_out;
     dd.idx_out = idx_out;
     dd.val_out = val_out;
@@ -899,6 +908,7 @@ dr_status roundtrip_impl(const float *g, const dr_config *cfg, uint8_t *payload,
         // stream runs it (once the caller's earlier work on s is done) while
         // the sender selects
         dd.w = qc.view((uint8_t *)ws + qoff);
+        dd.w.tiny = e.w.tiny;
         dd.w.qlist = e.w.qlist;
         dd.w.qbkt = e.w.qbkt;
         dd.w.qtab = e.w.qtab;
@@ -1046,7 +1056,8 @@ dr_status decode_sum_impl(const uint8_t *const *payloads, uint32_t npay, const d
     c.plan();
     if (!ws_ok(ws, ws_bytes, c.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", c.bytes);
-    const Work w = c.view((uint8_t *)ws);
+    Work w = c.view((uint8_t *)ws);
+    w.tiny = tiny_tensors(vt, c.ntiles);
     trace_call(s);
     DR_HIP(run_init(w, vt, s, true, {counts_out, counts_out ? 8 * T * npay : 0}));
     DR_HIP(launch_query_decode_sum(w, npay, (uint32_t)T, (uint32_t)ntiles1, scale, dense_out, counts_out, s));

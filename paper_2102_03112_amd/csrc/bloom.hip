@@ -774,6 +774,7 @@ __device__ __forceinline__ RecordView query_filter(const Work &w, const QueryOut
 // receiver's pass in us): resnet50_25m 157, 179 -> 128, 146; vgg16_138m 479,
 // 536 -> 401, 480; transformer_355m_x24 1250-1510, 2000 -> 1003, 1408.
 constexpr uint32_t RUN_TILES = 512;  // most tiles per run (LDS tile counters)
+constexpr uint32_t RUN_TENSORS = 32;  // most tensors per run
 
 // The tensor totals of the probe pass: the sender's |P| and values coded,
 // the plain query's count, or the receiver's |P| (checked against the
@@ -1223,6 +1224,64 @@ __device__ __forceinline__ void probe_window(const ProbeFilter &f, uint16_t *me,
     }
 }
 
+// A wave's window: ns steps from step `st` of a tile of the tensor at tile0,
+// d elements from `off`.  Writes its words of the positives bitmap and, for
+// the receiver, its zeros; returns its positives.
+template <int MODE>
+__device__ __forceinline__ uint32_t probe_take(const Work &w, const QueryOut &o, const ProbeFilter &f, bool pre,
+                                               bool part, bool all_lds, uint32_t J, uint64_t off, uint32_t tile0,
+                                               uint32_t d, uint32_t tile, uint32_t st, uint32_t ns, uint16_t *me,
+                                               uint32_t *mw) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wbase = (tile - tile0) * TILE + st * QWAVE;  // first index
+    const uint64_t word0 = (uint64_t)tile * TILE_WORDS + st * (QWAVE / 32);
+    const uint32_t nwords = ns * (QWAVE / 32);
+    const uint32_t nvalid = wbase < d ? min(d - wbase, ns * QWAVE) : 0u;
+    uint32_t word = 0;  // the window's bitmap, a word per lane
+    if (pre) word = lane < nwords ? w.pbits[word0 + lane] : 0u;
+    if (!pre) {
+        // the sender's selection is known to be positive
+        if (MODE == Q_ENCODE) word = lane < nwords ? w.selbits[word0 + lane] : 0u;
+        mw[lane] = word;
+        __builtin_amdgcn_wave_barrier();
+    }
+    float *dz = MODE == Q_DECODE ? o.dense_out + off + wbase : nullptr;
+    if (MODE == Q_DECODE && (pre || f.k == 0))
+        for (uint32_t s0 = 0; s0 < nvalid; s0 += QWAVE) zero_step(dz, s0, nvalid);
+    if (!pre) {
+        if (f.k > 0 && nvalid > 0) {
+            if (part)
+                probe_window<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
+            else if (all_lds)
+                probe_window<MODE, PK_LDS>(f, me, mw, wbase, nvalid, dz);
+            else if (J == 1)
+                probe_window<MODE, PK_SINGLE>(f, me, mw, wbase, nvalid, dz);
+            else
+                probe_window<MODE, PK_STANDARD>(f, me, mw, wbase, nvalid, dz);
+        }
+        word = mw[lane];
+        if (lane < nwords) w.pbits[word0 + lane] = word;
+    }
+    return wave_sum(lane < nwords ? (uint32_t)__popc(word) : 0u);
+}
+
+// The windows of a run of nq steps, in the order of their tickets: of WSTEPS
+// steps, then of two, then of one, so that the block's waves end together.
+struct Windows {
+    uint32_t w4, w2, n1;
+    __device__ __forceinline__ explicit Windows(uint32_t nq) {
+        n1 = min(nq, 2u * PB_WAVES);
+        const uint32_t n2 = min(nq - n1, 2u * PB_WAVES);
+        w4 = (nq - n1 - n2) / WSTEPS;
+        w2 = n2 / 2u;
+    }
+    __device__ __forceinline__ uint32_t count() const { return w4 + w2 + n1; }
+    __device__ __forceinline__ uint32_t steps(uint32_t q) const { return q < w4 ? WSTEPS : q < w4 + w2 ? 2u : 1u; }
+    __device__ __forceinline__ uint32_t first(uint32_t q) const {
+        return q < w4 ? q * WSTEPS : q < w4 + w2 ? w4 * WSTEPS + (q - w4) * 2u : w4 * WSTEPS + w2 * 2u + (q - w4 - w2);
+    }
+};
+
 template <int MODE>
 __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
     __shared__ uint32_t fc[FC_WORDS + 1];
@@ -1272,50 +1331,16 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
         const ProbeFilter f{fc, ps, buffer_view(rv.bits, rv.m_bits / 8u), uni(rv.m_bits), k, lim, J};
         uint16_t *me = qe[wv];
         uint32_t *mw = lw[wv];
-        // windows of WSTEPS steps, then of two, then of one, so that the
-        // block's waves end together
-        const uint32_t n1 = min(nq, 2u * PB_WAVES), n2 = min(nq - n1, 2u * PB_WAVES);
-        const uint32_t w4 = (nq - n1 - n2) / WSTEPS, w2 = n2 / 2u;
+        const Windows win(nq);
         for (;;) {
             uint32_t qi = 0;
             if (lane == 0) qi = atomicAdd(&next, 1u);
             qi = __builtin_amdgcn_readfirstlane(qi);
-            if (qi >= w4 + w2 + n1) break;
-            const uint32_t ns = qi < w4 ? WSTEPS : qi < w4 + w2 ? 2u : 1u;
-            const uint32_t st = qi < w4        ? qi * WSTEPS
-                                : qi < w4 + w2 ? w4 * WSTEPS + (qi - w4) * 2u
-                                               : w4 * WSTEPS + w2 * 2u + (qi - w4 - w2);
+            if (qi >= win.count()) break;
+            const uint32_t ns = win.steps(qi), st = win.first(qi);
             const uint32_t tile = rb + st / QPT;
-            const uint32_t wbase = (tile - tile0) * TILE + (st % QPT) * QWAVE;  // first index
-            const uint64_t word0 = (uint64_t)tile * TILE_WORDS + (st % QPT) * (QWAVE / 32);
-            const uint32_t nwords = ns * (QWAVE / 32);
-            const uint32_t nvalid = wbase < d ? min(d - wbase, ns * QWAVE) : 0u;
-            uint32_t word = 0;  // the window's bitmap, a word per lane
-            if (pre) word = lane < nwords ? w.pbits[word0 + lane] : 0u;
-            if (!pre) {
-                // the sender's selection is known to be positive
-                if (MODE == Q_ENCODE) word = lane < nwords ? w.selbits[word0 + lane] : 0u;
-                mw[lane] = word;
-                __builtin_amdgcn_wave_barrier();
-            }
-            float *dz = MODE == Q_DECODE ? o.dense_out + td.in.off + wbase : nullptr;
-            if (MODE == Q_DECODE && (pre || k == 0))
-                for (uint32_t s0 = 0; s0 < nvalid; s0 += QWAVE) zero_step(dz, s0, nvalid);
-            if (!pre) {
-                if (k > 0 && nvalid > 0) {
-                    if (part)
-                        probe_window<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
-                    else if (lim >= f.m_bits)
-                        probe_window<MODE, PK_LDS>(f, me, mw, wbase, nvalid, dz);
-                    else if (J == 1)
-                        probe_window<MODE, PK_SINGLE>(f, me, mw, wbase, nvalid, dz);
-                    else
-                        probe_window<MODE, PK_STANDARD>(f, me, mw, wbase, nvalid, dz);
-                }
-                word = mw[lane];
-                if (lane < nwords) w.pbits[word0 + lane] = word;
-            }
-            const uint32_t total = wave_sum(lane < nwords ? (uint32_t)__popc(word) : 0u);
+            const uint32_t total = probe_take<MODE>(w, o, f, pre, part, lim >= f.m_bits, J, td.in.off, tile0, d, tile,
+                                                    st % QPT, ns, me, mw);
             if (lane == 0) atomicAdd(&tcl[st / QPT], total);
             // the wave reconverges here, before the next window's ticket:
             // without it the compiler merged this lane-0 branch with
@@ -1323,6 +1348,132 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
             // the ticket's readfirstlane without lane 0, read window 0
             // from it again and again, and the pass never ended
             __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        for (uint32_t x = threadIdx.x; x < re - rb; x += PB_THREADS) w.tcnt[rb + x] = tcl[x];
+        rb = re;
+    }
+    __syncthreads();  // the block's tile counts are written; fc is free
+    probe_scan<MODE>(w, o, t_begin, t_end, fc);
+}
+
+// The same with runs of as many whole tensors as the LDS copy has room for,
+// so that a model's small layers share a run's set-up and barriers
+// (launch_probe).  A run's tensors are held one per lane.
+template <int MODE>
+__global__ __launch_bounds__(PB_THREADS) void k_probe_many(Work w, QueryOut o) {
+    __shared__ uint32_t fc[FC_WORDS + 1];
+    __shared__ uint16_t qe[PB_WAVES][QCAP];
+    __shared__ uint32_t lw[PB_WAVES][WSTEPS * QWAVE / 32];
+    __shared__ uint32_t tcl[RUN_TILES];
+    __shared__ uint32_t next;
+    __shared__ uint32_t ps[33];  // part starts of a partitioned filter
+    const uint32_t lane = threadIdx.x & 63u, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr uint32_t QPT = TILE / QWAVE;  // steps per tile
+    const Range32 own = probe_block_tiles(w.ntiles_total, gridDim.x, blockIdx.x);
+    const uint32_t t_begin = own.lo, t_end = own.hi;
+    uint32_t cached = 0xffffffffu;
+    for (uint32_t rb = t_begin; rb < t_end;) {
+        // lane l of each wave looks at tensor t0 + l
+        const uint32_t t0 = uni(tensor_of_tile(w, rb)), t = t0 + lane;
+        uint32_t v_tile0 = 0xffffffffu, v_end = 0, v_d = 0, v_m = 0, v_k = 0, v_words = 0, v_off[2] = {0, 0};
+        uint64_t v_bits = 0;
+        bool whole = false, bad = false, pre = false, part = false;
+        if (lane < RUN_TENSORS && t < w.ntensors && w.td[t].in.tile0 < t_end) {
+            TDesc &td = w.td[t];
+            bool ok;
+            const RecordView rv = query_filter(w, o, td, MODE, &ok);
+            bad = (MODE == Q_DECODE || MODE == Q_SUM) && !ok;
+            // a tensor the bucketed query has done: its positives bitmap is
+            // written, and the pass only counts it
+            pre = td.qb != 0u;
+            part = rv.layout == LAYOUT_PARTITIONED;
+            v_tile0 = td.in.tile0;
+            v_end = v_tile0 + td.in.ntiles;
+            v_d = td.in.d;
+            v_m = rv.m_bits;
+            v_k = rv.k;
+            v_off[0] = (uint32_t)td.in.off;
+            v_off[1] = (uint32_t)(td.in.off >> 32);
+            v_bits = (uint64_t)(uintptr_t)rv.bits;
+            v_words = pre ? 0u : min(rv.m_bits / 32u, FC_WORDS);
+            whole = !pre && !part && rv.m_bits / 32u <= FC_WORDS;
+        }
+        const uint32_t upto = wave_incl_scan(v_words);
+        const uint64_t fits = ballot(whole && upto <= FC_WORDS && (lane == 0 || v_end <= rb + RUN_TILES));
+        // tensors of the run; at least the first, whatever its filter
+        const uint32_t nrun = max(1u, (uint32_t)__ffsll((unsigned long long)~fits) - 1u);
+        const bool all_lds = (fits & 1u) != 0u;
+        pre = (ballot(pre) & 1u) != 0u;  // of the first tensor, the only one unless LDS holds all
+        part = (ballot(part) & 1u) != 0u;
+        const uint32_t v_base = upto - v_words;
+        const uint32_t re = min(min(t_end, (uint32_t)__builtin_amdgcn_readlane(v_end, nrun - 1)), rb + RUN_TILES);
+        const uint32_t nq = (re - rb) * QPT;
+        __syncthreads();  // the previous run is finished with fc, tcl and next
+        if (t0 != cached || nrun > 1) {
+            // 64 words of one filter at a time, eight such pieces of a wave
+            // in flight together
+            const uint32_t v_pieces = lane < nrun ? (v_words + 63u) / 64u : 0u;
+            const uint32_t pieces_to = wave_incl_scan(v_pieces), v_piece0 = pieces_to - v_pieces;
+            const uint32_t npieces = __builtin_amdgcn_readlane(pieces_to, 63);
+            for (uint32_t q0 = wv; q0 < npieces; q0 += PB_WAVES * 8) {
+                uint32_t val[8], at[8];
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u) {
+                    const uint32_t q = q0 + u * PB_WAVES;
+                    at[u] = 0xffffffffu;
+                    if (q < npieces) {
+                        const uint32_t sl = popc64(ballot(lane < nrun && v_piece0 <= q && v_pieces > 0)) - 1;
+                        const uint32_t x = (q - __builtin_amdgcn_readlane(v_piece0, sl)) * 64 + lane;
+                        const uint64_t ptr = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v_bits >> 32), sl) << 32) |
+                                             (uint32_t)__builtin_amdgcn_readlane((uint32_t)v_bits, sl);
+                        if (x < (uint32_t)__builtin_amdgcn_readlane(v_words, sl)) {
+                            val[u] = ((const uint32_t *)(uintptr_t)ptr)[x];
+                            at[u] = __builtin_amdgcn_readlane(v_base, sl) + x;
+                        }
+                    }
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u)
+                    if (at[u] != 0xffffffffu) fc[at[u]] = val[u];
+            }
+            if (!all_lds && !pre) {
+                if (threadIdx.x == 0) fc[v_words] = 0xffffffffu;
+                if (part) fill_part_starts(ps, uni(v_m), uni(v_k));
+            }
+            cached = nrun > 1 ? 0xffffffffu : t0;
+        }
+        for (uint32_t x = threadIdx.x; x < re - rb; x += PB_THREADS) tcl[x] = 0;
+        if (threadIdx.x == 0) next = 0;
+        if (wv == 0 && lane < nrun && bad) {
+            atomicOr(&w.td[t].flags, FLAG_DEC_MISMATCH);
+            if (o.counts_out) atomicOr((unsigned long long *)&o.counts_out[4 * t + 3], FLAG_DEC_MISMATCH);
+        }
+        __syncthreads();
+        const uint32_t m0 = uni(v_m), lim0 = uni(v_words) * 32u;
+        const __amdgpu_buffer_rsrc_t bits0 = buffer_view((const void *)(uintptr_t)uni(v_bits), m0 / 8u);
+        const uint32_t J0 = uni(probe_hashes(m0, uni(v_k), lim0, part ? LAYOUT_PARTITIONED : LAYOUT_STANDARD));
+        uint16_t *me = qe[wv];
+        uint32_t *mw = lw[wv];
+        const Windows win(nq);
+        for (;;) {
+            uint32_t qi = 0;
+            if (lane == 0) qi = atomicAdd(&next, 1u);
+            qi = __builtin_amdgcn_readfirstlane(qi);
+            if (qi >= win.count()) break;
+            const uint32_t ns = win.steps(qi), st = win.first(qi);
+            const uint32_t tile = rb + st / QPT;
+            const uint32_t sl = popc64(ballot(lane < nrun && v_tile0 <= tile)) - 1;  // the tile's tensor
+            const uint32_t k = __builtin_amdgcn_readlane(v_k, sl);
+            const ProbeFilter f{fc + __builtin_amdgcn_readlane(v_base, sl), ps, bits0,
+                                (uint32_t)__builtin_amdgcn_readlane(v_m, sl), k, lim0, all_lds ? min(2u, max(k, 1u)) : J0};
+            const uint64_t off = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(v_off[1], sl) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane(v_off[0], sl);
+            const uint32_t total =
+                probe_take<MODE>(w, o, f, pre, part, all_lds, J0, off, __builtin_amdgcn_readlane(v_tile0, sl),
+                                 __builtin_amdgcn_readlane(v_d, sl), tile, st % QPT, ns, me, mw);
+            if (lane == 0) atomicAdd(&tcl[st / QPT], total);
+            __builtin_amdgcn_wave_barrier();  // the wave reconverges here, as in k_probe
         }
         __syncthreads();
         for (uint32_t x = threadIdx.x; x < re - rb; x += PB_THREADS) w.tcnt[rb + x] = tcl[x];
@@ -1993,6 +2144,20 @@ static int probe_grid(const Work &w) {
     return (int)std::max(1u, std::min(cus, by_tiles));
 }
 
+// Runs of several tensors where some are smaller than a block's share of the
+// tiles (a model's biases and small layers): a run each would make the block
+// that holds the most of them the last to finish (161 layers of 25.6 M
+// elements: receiver's pass 113 us with a run each, 80 with shared ones).
+// The lookups cost the pass of a few large tensors 3%, so these keep a run
+// each (24 tensors, 355 M elements: 1408 against 1458 us).
+template <int MODE>
+static void launch_probe(const Work &w, const QueryOut &o, int grid, hipStream_t s) {
+    if (w.tiny > 0)
+        k_probe_many<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
+    else
+        k_probe<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
+}
+
 hipError_t launch_query_encode(const Work &w, const float *g, int grid_persist, uint64_t *counts_out, hipStream_t s,
                                hipEvent_t after_probe) {
     QueryOut o{};
@@ -2001,7 +2166,7 @@ hipError_t launch_query_encode(const Work &w, const float *g, int grid_persist, 
     o.counts_out = counts_out;
     // the pass also scans its tile counts (probe_scan) and writes the
     // records' headers
-    k_probe<Q_ENCODE><<<probe_grid(w), PB_THREADS, 0, s>>>(w, o);
+    launch_probe<Q_ENCODE>(w, o, probe_grid(w), s);
     trace_mark(s, "k_probe<Q_ENCODE>");
     if (after_probe) {
         hipError_t e = hipEventRecord(after_probe, s);
@@ -2041,7 +2206,7 @@ hipError_t launch_query_plain(const Work &w, uint32_t *idx_out, uint64_t cap, ui
     o.cap = cap;
     o.n_out = n_out;
     // the pass also scans its tile counts (probe_scan)
-    k_probe<Q_PLAIN><<<probe_grid(w), PB_THREADS, 0, s>>>(w, o);
+    launch_probe<Q_PLAIN>(w, o, probe_grid(w), s);
     trace_mark(s, "k_probe<Q_PLAIN>");
     k_emit<Q_PLAIN><<<resident_grid(k_emit<Q_PLAIN>, EMIT_THREADS, w.ntiles_total), EMIT_THREADS, 0, s>>>(w, o);
     trace_mark(s, "k_emit<Q_PLAIN>");
@@ -2056,7 +2221,7 @@ hipError_t launch_probe_decode(const Work &w, float *dense_out, uint64_t *counts
     // std::min: HIP's host min() takes ints, and max_blocks may be ~0u
     const uint32_t grid = std::min<uint32_t>((uint32_t)probe_grid(w), std::max<uint32_t>(1u, max_blocks));
     // the pass also scans its tile counts (probe_scan)
-    k_probe<Q_DECODE><<<grid, PB_THREADS, 0, s>>>(w, o);
+    launch_probe<Q_DECODE>(w, o, (int)grid, s);
     trace_mark(s, "k_probe<Q_DECODE>");
     return hipGetLastError();
 }
@@ -2087,7 +2252,7 @@ hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens,
     o.ntens = ntens;
     o.ntiles1 = ntiles1;
     // the pass also scans its tile counts (probe_scan)
-    k_probe<Q_SUM><<<probe_grid(w), PB_THREADS, 0, s>>>(w, o);
+    launch_probe<Q_SUM>(w, o, probe_grid(w), s);
     trace_mark(s, "k_probe<Q_SUM>");
     k_emit_sum<<<resident_grid(k_emit_sum, NTHREADS, ntiles1), NTHREADS, 0, s>>>(w, o);
     trace_mark(s, "k_emit_sum");

@@ -54,3 +54,19 @@ def test_round_trip_with_large_filters(d, ratio, fpr, layout):
     cfg = B.Config([0, d], ratio, fpr, 3, 4, filter_layout=layout)
     refs = oracle.roundtrip(g, [0, d], ratio, fpr, 3, 4, layout=layout)
     check_roundtrip(g, cfg, run_roundtrip(g, cfg), refs)
+
+
+@pytest.mark.parametrize("layout", [0, 1], ids=["standard", "partitioned"])
+@pytest.mark.parametrize("tensors,spread", [(300, 4000), (67, 40_000), (40, 1)])
+def test_round_trip_of_many_tensors(tensors, spread, layout):
+    """Blocks whose runs hold many tensors at once, empty and one-element
+    tensors among them, and set-up over several launches."""
+    rng = np.random.default_rng(tensors)
+    sizes = rng.integers(0, spread + 1, tensors)
+    sizes[tensors // 2] = 300_000  # a filter larger than what LDS keeps
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    log(f"{tensors} tensors, {int(off[-1])} elements")
+    g = (rng.standard_normal(int(off[-1])) * 1e-3).astype(np.float32)
+    cfg = B.Config(off, (1, 4), 1e-3, 3, 2, filter_layout=layout)
+    refs = oracle.roundtrip(g, off, (1, 4), 1e-3, 3, 2, layout=layout)
+    check_roundtrip(g, cfg, run_roundtrip(g, cfg), refs)
