@@ -93,11 +93,15 @@ struct Carve {
     // values the sender expects to code (r per top-r tensor, doubled for its
     // false positives; d for the support): sizes the reorder-map packing grid
     uint64_t vals_est = 0;
+    // bucket sort: buckets reserved, whether some tensor may have several,
+    // and pairs of its own (the round trip's lie in the selection's arrays)
+    uint64_t bs_total = 0, bs_pairs = 0;
+    bool bs_multi = false;
     bool query_only = false;  // descriptors, tile counts, the positives bitmap and the tile table only
     size_t bytes = 0;
     size_t o_td, o_glob, o_pstat, o_histA, o_shist, o_fcnt, o_tcnt, o_toff, o_ccnt, o_hist, o_sel, o_pbits, o_ckey, o_cidx, o_S, o_P,
         o_V, o_sstat, o_sdig, o_ttab, o_fit, o_btab, o_brow, o_keyA, o_keyB, o_valA, o_valB, o_sig, o_vs, o_bnd,
-        o_segst, o_segpart, o_qlist, o_qbkt, o_qtab, o_qrow;
+        o_segst, o_segpart, o_bscnt, o_bsspl, o_bspair, o_qlist, o_qbkt, o_qtab, o_qrow;
 
     void plan() {
         size_t at = 0;
@@ -138,6 +142,11 @@ struct Carve {
         o_bnd = take(all * 4 * bnd);
         o_segst = take(all * sizeof(SegState) * segslots);
         o_segpart = take(all * sizeof(SegPart) * SEG_GRID_BLOCKS * segslots);
+        o_bscnt = take(all * 4 * bs_total);
+        o_bsspl = take(all * 8 * bs_total);
+        // after the selection its candidates, index lists and value copy are
+        // free: 2.5 pairs per slot
+        o_bspair = bs_pairs ? take(all * 8 * bs_pairs) : o_ckey;
         o_keyA = take(all * 4 * slots);
         o_keyB = take(all * 4 * slots);
         o_valA = take(all * 4 * slots);
@@ -189,6 +198,11 @@ struct Carve {
         w.bounds = (uint32_t *)(ws + o_bnd);
         w.segst = (SegState *)(ws + o_segst);
         w.segpart = (SegPart *)(ws + o_segpart);
+        w.bscnt = (uint32_t *)(ws + o_bscnt);
+        w.bsspl = (uint64_t *)(ws + o_bsspl);
+        w.bspair = (uint64_t *)(ws + o_bspair);
+        w.bstotal = (uint32_t)bs_total;
+        w.bsmulti = bs_multi ? 1u : 0u;
         w.qlist = (uint32_t *)(ws + o_qlist);
         w.qbkt = (uint32_t *)(ws + o_qbkt);
         w.qtab = (uint32_t *)(ws + o_qtab);
@@ -271,6 +285,7 @@ Carve bound_carve(uint64_t d, uint64_t n_tensors) {
     // gives -ln(fpr) / (ln 2)^2 < 47 bits per item); plus one filter of
     // BL_MAX_SLICES for a standalone insert whose filter is larger than its
     // item count
+    c.bs_total = 2 * c.ntiles;
     c.bslices = 47 * c.slots / (1u << SLICE_LOG2_MIN) + 2 * n_tensors + BL_MAX_SLICES;
     c.btab = c.bslices * MAX_CHUNKS;
     // the bucketed query of one tensor of at most d elements: at most
@@ -400,6 +415,45 @@ void plan_bloom_direct(Plan &p, bool from_bitmap) {
     p.dir_slices = (uint32_t)sl;
 }
 
+// The bucket sort, when every tensor is expected to code few enough values:
+// `most` is each tensor's bound on them (the planned count, or eight standard
+// deviations above the expected one; a tensor that codes more still sorts,
+// with fuller buckets).  Its buckets must fit in the tensor's 2 pairs per
+// slot, or in pairs of their own (`own_pairs`, one tensor).  The radix sort
+// takes five launches whose tiles wait for each other; the bucket sort one
+// for tensors of one bucket and three otherwise.
+void plan_bucket_sort(Plan &p, const std::vector<uint64_t> &most, bool own_pairs) {
+    uint64_t total = 0;
+    bool multi = false;
+    std::vector<uint32_t> n(most.size());
+    for (size_t t = 0; t < most.size(); ++t) {
+        n[t] = (uint32_t)(most[t] <= BS_CAP ? 1 : std::min<uint64_t>(BS_MAX_BUCKETS + 1, ceil_div(most[t], BS_AVG)));
+        if (n[t] > BS_MAX_BUCKETS) return;
+        if (n[t] > 1 && !own_pairs && (uint64_t)n[t] * BS_CAP > 2ull * p.t[t].ntiles * TILE) return;
+        multi |= n[t] > 1;
+        total += n[t];
+    }
+    uint32_t at = 0;
+    for (size_t t = 0; t < most.size(); ++t) {
+        p.t[t].bs0 = at;
+        p.t[t].bsn = n[t];
+        at += n[t];
+    }
+    p.carve.bs_total = total;
+    p.carve.bs_multi = multi;
+    p.carve.bs_pairs = own_pairs && multi ? total * BS_CAP : 0;
+}
+
+// Values a top-r tensor is expected to code at most: its r, and under P0 the
+// false positives of an m-bit filter of r items with k hashes.
+uint64_t values_bound(uint64_t d, uint64_t r, uint64_t m, uint32_t k, uint32_t policy) {
+    if (policy != DR_POLICY_P0) return r;
+    double fill = 1.0 - std::exp(-(double)k * (double)r / (double)m);
+    fill = std::min(1.0, fill + 8.0 * std::sqrt(fill * (1.0 - fill) / (double)m));  // of a small filter
+    const double fp = std::pow(fill, (double)k) * (double)(d - r);
+    return std::min<uint64_t>(d, r + (uint64_t)(1.02 * fp + 8.0 * std::sqrt(fp) + 64.0));
+}
+
 // The receiver's bucketed query, for tensors whose filter may be larger
 // than an XCD's L2: those of at most QB_MAX_D elements whose largest filter (m for their
 // n_cap items) has at least qb_min_bits() bits, the first QB_MAX_TENSORS of
@@ -506,6 +560,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     p.t.resize(T);
     rec_off.assign(T + 1, 0);
     uint64_t tiles = 0, hist_blocks = 0, redo_blocks = 0, fit_blocks = 0, bnd = 0;
+    std::vector<uint64_t> most(T);
     p.carve = Carve();
     uint64_t all_tiles = 0;
     for (uint64_t t = 0; t < T; ++t) {
@@ -575,6 +630,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
             in.rb0 = (uint32_t)redo_blocks;
             in.rbn = 0;
         }
+        most[t] = nz ? d : values_bound(d, r, m_cap, kk, cfg->policy);
         plan_bloom(in, n_cap, m_cap, true, p);
         rec_off[t + 1] = rec_off[t] + align_up(record_capacity(d, n_cap, cfg->fpr, degree, runs,
                                                                cfg->segmentation == DR_SEG_CHORD),
@@ -589,6 +645,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     p.carve.fit_blocks = fit_blocks;
     p.carve.bnd = bnd;
     plan_query_bucketed(p, allow_qb);
+    plan_bucket_sort(p, most, false);
     p.carve.plan();
     plan_bloom_rounds(p, k);
     plan_bloom_direct(p, true);
@@ -638,7 +695,10 @@ hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, b
     z.z[1] = {w.pstat, 2ull * PSTAT_MAX};
     z.n = 2;
     if (!query_only) {
-        z.z[z.n++] = {w.sdig, 4ull * SORT_BINS * w.ntensors};
+        if (w.bstotal)
+            z.z[z.n++] = {w.bscnt, w.bstotal};
+        else
+            z.z[z.n++] = {w.sdig, 4ull * SORT_BINS * w.ntensors};
         // hist, histA, shist and fcnt (carved one after the other)
         z.z[z.n++] = {w.hist, (uint64_t)(((uint8_t *)w.fcnt - (uint8_t *)w.hist) / 4) +
                                   (uint64_t)FCNT_COPIES * FCNT_W * w.ntensors};
@@ -1216,6 +1276,24 @@ void check_sort_tiles(const Plan &p, RangeCheck &rc) {
                (unsigned long long)c.ntiles);
 }
 
+// The bucket sort's buckets: consecutive over the tensors, each tensor's
+// pairs within its share of the selection's arrays.
+void check_bucket_sort(const Plan &p, RangeCheck &rc) {
+    const Carve &c = p.carve;
+    if (!c.bs_total) return;
+    uint64_t at = 0;
+    for (size_t t = 0; t < p.t.size(); ++t) {
+        const TInit &in = p.t[t];
+        rc.fail_if(in.bs0 != at || in.bsn < 1 || in.bsn > BS_MAX_BUCKETS, "tensor %zu: %u buckets from %u", t, in.bsn,
+                   in.bs0);
+        rc.fail_if(in.bsn > 1 && (uint64_t)in.bsn * BS_CAP > 2ull * in.ntiles * TILE,
+                   "tensor %zu: %u buckets in %u tiles' room", t, in.bsn, in.ntiles);
+        at += in.bsn;
+    }
+    rc.fail_if(at != c.bs_total, "%llu buckets of %llu", (unsigned long long)at, (unsigned long long)c.bs_total);
+    rc.fail_if(c.o_bspair + 16 * c.slots > c.o_V, "the buckets' pairs end past the selection's arrays");
+}
+
 dr_status check_ranges_impl(const dr_config *cfg, uint64_t *violations) {
     if (!violations) return fail(DR_EINVAL, "violations_h is null");
     Plan p;
@@ -1230,6 +1308,7 @@ dr_status check_ranges_impl(const dr_config *cfg, uint64_t *violations) {
         check_bucketed(p, rc);
     check_probe_blocks((uint32_t)p.carve.ntiles, rc);
     check_sort_tiles(p, rc);
+    check_bucket_sort(p, rc);
     // the standalone insert of each tensor's selection (dr_bloom_encode's
     // plan: items from a list of n_cap entries)
     for (size_t t = 0; t < p.t.size(); ++t) {
@@ -1541,7 +1620,14 @@ dr_status dr_curvefit_encode(const float *vals, const uint64_t *n, uint64_t n_ca
     in.sigma = sigma_out;
     in.fit_blk0 = 0;
     p.carve.fit_blocks = (uint64_t)n_seg * FIT_CHUNKS;
+    plan_bucket_sort(p, {n_cap}, true);
     p.carve.plan();
+    if (ws_bytes < p.carve.bytes && p.carve.bs_pairs) {  // no room for the buckets: the radix sort
+        in.bs0 = in.bsn = 0;
+        p.carve.bs_total = p.carve.bs_pairs = 0;
+        p.carve.bs_multi = false;
+        p.carve.plan();
+    }
     if (!ws_ok(ws, ws_bytes, p.carve.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", p.carve.bytes);
     const Work w = p.carve.view((uint8_t *)ws);

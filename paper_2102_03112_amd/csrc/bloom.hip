@@ -2043,9 +2043,8 @@ __global__ __launch_bounds__(EMIT_THREADS) EMIT_WAVES_PER_EU(GEN) void k_emit(Wo
                     // (tslot is a multiple of the tile, so bit i & 31)
                     if (sparse_vals && !((w.selbits[(tslot + i) >> 5] >> (i & 31u)) & 1u)) x = 0.0f;
                     const uint64_t at = tslot + vn;
-                    w.V[at] = x;
                     w.keyA[at] = ~order_key(x);  // ascending order of ~key = descending values
-                    w.valA[at] = vn;
+                    if (!w.bstotal) w.valA[at] = vn;  // the bucket sort has it from the place
                 }
             } else if (MODE == Q_PLAIN) {
                 if (q < o.cap) o.idx_out[q] = i;

@@ -74,6 +74,15 @@ constexpr uint32_t HISTA_BINS = NBR * 1024;      // candidate histogram: (bin - 
 constexpr uint32_t FCNT_COPIES = 16;
 constexpr uint32_t FCNT_W = 1 + NBR;
 constexpr uint32_t SORT_BINS = 256;           // 8-bit LSD radix digits
+// Bucket sort of the values (tensors expected to code at most BS_MAX_BUCKETS
+// x BS_AVG): values are dealt to buckets of about BS_AVG by splitters from a
+// sample, then each bucket is sorted in LDS, which holds BS_CAP.  With
+// BS_OVER samples per bucket a bucket of random sample positions exceeds
+// BS_CAP = 4 BS_AVG with probability about exp(-16 (3 - ln 4)) = 6e-12.
+constexpr uint32_t BS_CAP = 4096;
+constexpr uint32_t BS_AVG = 1024;
+constexpr uint32_t BS_OVER = 16;
+constexpr uint32_t BS_MAX_BUCKETS = 512;
 constexpr uint32_t FIT_CHUNKS = 8;            // partial-moment blocks per fitted run
 constexpr uint32_t MAX_DEG = 7;
 constexpr uint32_t MAX_SEG = 4096;            // most runs per tensor
@@ -154,6 +163,7 @@ struct TInit {
     uint32_t nsamp;      // elements in the sample
     uint32_t slo, shi;   // sample ranks that bound the bracket: rho -/+ delta
     uint32_t rb0, rbn;   // blocks of the full histogram for a redo
+    uint32_t bs0, bsn;   // bucket sort: first bucket of this tensor, buckets reserved (0: the radix sort)
 };
 
 // Chord segmentation over the whole grid (at most SEG_GRID_RUNS runs per
@@ -268,6 +278,13 @@ struct Work {
     uint32_t *srow;           // sort: per tensor digit totals
     uint32_t *sig;            // unpacked reorder map, per tensor slot
     float *vsorted;           // values in sorted order, per tensor slot
+    // bucket sort: values per bucket, each bucket's least (key, value number),
+    // and the buckets' values (bucket b of a tensor at 2 slot + b BS_CAP)
+    uint32_t *bscnt;
+    uint64_t *bsspl;
+    uint64_t *bspair;
+    uint32_t bstotal;         // buckets reserved over all tensors (0: the radix sort)
+    uint32_t bsmulti;         // some tensor may have several
     double *fit_part;         // fit: partial moments
     uint32_t fit_runs;
     uint32_t *bpos;           // Bloom insert: bucketed in-slice positions

@@ -113,6 +113,7 @@ hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens,
 hipError_t launch_keygen(const Work &w, const float *vals, const uint64_t *n, uint64_t n_cap, uint64_t *flags_out,
                          int grid_persist, hipStream_t s);
 hipError_t launch_value_setup(const Work &w, bool payload, uint64_t *counts_out, hipStream_t s);
+// the bucket sort if the work has buckets, else the radix sort
 hipError_t launch_sort(const Work &w, uint32_t cap_tiles, hipStream_t s);
 hipError_t launch_segment(const Work &w, uint32_t grid_req, bool block_pass, hipStream_t s);
 // the fit's moments with the packing of the reorder maps (one launch), the

@@ -1,0 +1,90 @@
+"""The bucket sort of the values: one bucket, the edges of one and of several,
+ties of every kind, and a bucket that outgrows its room.  Reorder map and
+coefficients against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2102_03112_amd import binding as B
+from _gpu_util import check_roundtrip, dev_tensor, host, log, run_roundtrip, sync, u64_scalar, workspace
+
+pytestmark = pytest.mark.gpu
+
+CAP, AVG, OVER = 4096, 1024, 16  # a bucket's room and mean size, samples per bucket
+
+
+def _m32(x):
+    return x & 0xFFFFFFFF
+
+
+def sample_places(n):
+    """Where the sort takes its sample of n > CAP values from."""
+    S = -(-n // AVG) * OVER
+    i = np.arange(S, dtype=np.uint64)
+    a, e = i * np.uint64(n) // np.uint64(S), (i + np.uint64(1)) * np.uint64(n) // np.uint64(S)
+    h = np.array([oracle.murmur3_32(int(q).to_bytes(4, "little"), 0x5EED) for q in i], dtype=np.uint64)
+    return (a + (h * (e - a) >> np.uint64(32))).astype(np.int64)
+
+
+def values(kind, n, rng):
+    if kind == "normal":
+        return rng.standard_normal(n)
+    if kind == "equal":
+        return np.full(n, 0.25)
+    if kind == "zeros":  # signed zeros among values, as false positives with sparse values
+        return np.where(rng.random(n) < 0.3, np.where(rng.random(n) < 0.5, 0.0, -0.0), rng.standard_normal(n))
+    if kind == "coarse":
+        return rng.integers(-9, 10, n) * 0.25
+    if kind == "sorted":
+        return np.sort(rng.standard_normal(n))
+    if kind == "outgrown":  # every sampled value is the same, so one bucket gets all the others
+        v = 2.0 + rng.random(n)
+        v[sample_places(n)] = 1.0
+        return v
+    if kind == "wide":  # both ends of the range of floats
+        return rng.standard_normal(n) * 10.0 ** rng.integers(-40, 38, n)
+    raise ValueError(kind)
+
+
+SIZES = [1, 2, 63, 513, CAP - 1, CAP, CAP + 1, 8191, 20_000, 100_001, 512 * AVG, 512 * AVG + 1]
+CASES = [(n, "normal") for n in SIZES] + [(n, k) for n in (CAP, 30_000) for k in ("equal", "zeros", "coarse", "sorted", "wide")]
+
+
+@pytest.mark.parametrize("n,kind", CASES + [(30_000, "outgrown")])
+def test_reorder_map(n, kind):
+    import torch
+
+    log(f"sort n={n} kind={kind}")
+    v = values(kind, n, np.random.default_rng(n)).astype(np.float32)
+    ref = oracle.curvefit_encode(v, 3, 4)
+    nd = torch.tensor([n], dtype=torch.int64, device="cuda")
+    coef = torch.zeros(16, dtype=torch.float32, device="cuda")
+    sigma = torch.zeros((n * B.sigma_bits(n) + 31) // 32, dtype=torch.int32, device="cuda")
+    B.curvefit_encode(dev_tensor(v), nd, n, 3, 4, coef, sigma, workspace(8 * n))
+    sync()
+    np.testing.assert_array_equal(host(sigma).view(np.uint32), ref.sigma)
+
+
+def test_workspace_without_room_for_buckets():
+    """The exact workspace of so many values: the radix sort instead."""
+    import torch
+
+    n = 50_000
+    v = np.random.default_rng(1).standard_normal(n).astype(np.float32)
+    nd = torch.tensor([n], dtype=torch.int64, device="cuda")
+    coef = torch.zeros(16, dtype=torch.float32, device="cuda")
+    sigma = torch.zeros((n * B.sigma_bits(n) + 31) // 32, dtype=torch.int32, device="cuda")
+    B.curvefit_encode(dev_tensor(v), nd, n, 3, 4, coef, sigma, B.workspace(n))
+    sync()
+    np.testing.assert_array_equal(host(sigma).view(np.uint32), oracle.curvefit_encode(v, 3, 4).sigma)
+
+
+@pytest.mark.parametrize("source", [B.VALUES_DENSE, B.VALUES_SPARSE], ids=["dense", "sparse"])
+@pytest.mark.parametrize("sizes,ratio", [([700_000], (1, 50)), ([100, 400_000, 0, 41_000, 1, 900_000], (1, 20)),
+                                         ([200_000], (1, 2))])
+def test_round_trip(sizes, ratio, source):
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    g = (np.random.default_rng(7).standard_normal(int(off[-1])) * 1e-3).astype(np.float32)
+    cfg = B.Config(off, ratio, 1e-2, 3, 4, value_source=source)
+    refs = oracle.roundtrip(g, off, ratio, 1e-2, 3, 4, value_source=source)
+    check_roundtrip(g, cfg, run_roundtrip(g, cfg), refs)
