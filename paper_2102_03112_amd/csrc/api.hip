@@ -85,7 +85,7 @@ int persist_grid(int per_cu) { return dr::device_cus() * per_cu; }
 // entries (padded elements); the last six are contiguous so the Bloom insert
 // can borrow them for its position buffer before the value path needs them.
 struct Carve {
-    uint64_t slots = 0, ntiles = 0, ntensors = 0, hist_blocks = 0, redo_blocks = 0, fit_blocks = 0, btab = 0,
+    uint64_t slots = 0, ntiles = 0, ntensors = 0, hist_blocks = 0, redo_blocks = 0, fit_blocks = 0, fit_runs = 0, btab = 0,
              bslices = 0, bnd = 0, segslots = 0;
     // bucketed query: list entries (the largest such tensor's size), count
     // table words and round-total words; both carves hold them
@@ -184,7 +184,6 @@ struct Carve {
         w.sdig = (uint32_t *)(ws + o_sdig);
         w.tile_tensor = (uint32_t *)(ws + o_ttab);
         w.fit_part = (double *)(ws + o_fit);
-        w.fit_runs = (uint32_t)(fit_blocks / FIT_CHUNKS);
         w.btab = (uint32_t *)(ws + o_btab);
         w.brow = (uint32_t *)(ws + o_brow);
         w.bslices = (uint32_t)bslices;
@@ -444,6 +443,14 @@ void plan_bucket_sort(Plan &p, const std::vector<uint64_t> &most, bool own_pairs
     p.carve.bs_pairs = own_pairs && multi ? total * BS_CAP : 0;
 }
 
+// Partial-moment blocks for a run of at most ns points (the kernel's chunks of
+// 2048 at least); the double exponential keeps its state in the run's share of
+// the partials.
+uint32_t fit_blocks_per_run(uint64_t ns, uint32_t model) {
+    if (model == DR_FIT_DEXP) return FIT_CHUNKS;
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(FIT_CHUNKS, ceil_div(ns, FIT_MIN_CHUNK)));
+}
+
 // Values a top-r tensor is expected to code at most: its r, and under P0 the
 // false positives of an m-bit filter of r items with k hashes.
 uint64_t values_bound(uint64_t d, uint64_t r, uint64_t m, uint32_t k, uint32_t policy) {
@@ -559,7 +566,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     if (!bloom_params_host(1, cfg->fpr, &m_any, &k)) return fail(DR_EINVAL, "fpr gives more than 32 hashes");
     p.t.resize(T);
     rec_off.assign(T + 1, 0);
-    uint64_t tiles = 0, hist_blocks = 0, redo_blocks = 0, fit_blocks = 0, bnd = 0;
+    uint64_t tiles = 0, hist_blocks = 0, redo_blocks = 0, fit_blocks = 0, fit_runs = 0, bnd = 0;
     std::vector<uint64_t> most(T);
     p.carve = Carve();
     uint64_t all_tiles = 0;
@@ -605,8 +612,16 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
         // top-r: |S| = r is known, so the filter size is too
         in.m_words_in = nz ? 0u : (uint32_t)(m_cap / 32);
         const uint64_t runs = runs_cap(d, degree, cfg->n_seg);
+        most[t] = nz ? d : values_bound(d, r, m_cap, kk, cfg->policy);
+        // equal runs of a requested number share the values evenly; a chord
+        // run or one of a heuristic number may hold them all
+        const bool even = cfg->segmentation == DR_SEG_EQUAL && cfg->n_seg >= 1;
+        in.fit_run0 = (uint32_t)fit_runs;
         in.fit_blk0 = (uint32_t)fit_blocks;
-        fit_blocks += runs * FIT_CHUNKS;
+        in.fch = fit_blocks_per_run(even ? ceil_div(most[t], runs_cap(most[t], degree, cfg->n_seg)) : most[t],
+                                    cfg->fit_model);
+        fit_runs += runs;
+        fit_blocks += runs * in.fch;
         in.seg_slot = NO_SEG_SLOT;
         if (cfg->segmentation == DR_SEG_CHORD) {
             in.bnd0 = (uint32_t)bnd;
@@ -630,7 +645,6 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
             in.rb0 = (uint32_t)redo_blocks;
             in.rbn = 0;
         }
-        most[t] = nz ? d : values_bound(d, r, m_cap, kk, cfg->policy);
         plan_bloom(in, n_cap, m_cap, true, p);
         rec_off[t + 1] = rec_off[t] + align_up(record_capacity(d, n_cap, cfg->fpr, degree, runs,
                                                                cfg->segmentation == DR_SEG_CHORD),
@@ -643,6 +657,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     p.carve.hist_blocks = hist_blocks;
     p.carve.redo_blocks = redo_blocks;
     p.carve.fit_blocks = fit_blocks;
+    p.carve.fit_runs = fit_runs;
     p.carve.bnd = bnd;
     plan_query_bucketed(p, allow_qb);
     plan_bucket_sort(p, most, false);
@@ -653,29 +668,46 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
 }
 
 // The words in which the call's descriptors differ from the first, grouped
-// into columns of equal differences.
+// into columns of equal differences: first those that need 32 bits, then those
+// that 16 hold.  src: the descriptor word that each column follows.
 void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t> &src) {
     a.base = t[0];
     const uint32_t *base = (const uint32_t *)&a.base;
+    auto diff = [&](size_t c, uint32_t i) { return ((const uint32_t *)&t[c])[i] - base[i]; };
+    std::vector<uint32_t> wide, narrow;
+    uint32_t follows[TINIT_WORDS];  // the word whose column word i shares
     for (uint32_t i = 0; i < TINIT_WORDS; ++i) {
-        a.col[i] = INIT_SAME;
-        bool same = true;
-        for (size_t c = 1; c < t.size() && same; ++c) same = ((const uint32_t *)&t[c])[i] == base[i];
-        if (same) continue;
-        for (size_t k = 0; k < src.size() && a.col[i] == INIT_SAME; ++k) {
-            bool alike = true;
-            for (size_t c = 1; c < t.size() && alike; ++c) {
-                const uint32_t *w = (const uint32_t *)&t[c];
-                alike = w[i] - base[i] == w[src[k]] - base[src[k]];
-            }
-            if (alike) a.col[i] = (uint8_t)k;
+        follows[i] = TINIT_WORDS;
+        bool same = true, small = true;
+        for (size_t c = 1; c < t.size(); ++c) {
+            const uint32_t x = diff(c, i);
+            same &= x == 0;
+            small &= (int32_t)x == (int16_t)x;
         }
-        if (a.col[i] == INIT_SAME) {
-            a.col[i] = (uint8_t)src.size();
-            src.push_back(i);
+        if (same) continue;
+        std::vector<uint32_t> &cols = small ? narrow : wide;
+        for (uint32_t k : cols) {
+            bool alike = true;
+            for (size_t c = 1; c < t.size() && alike; ++c) alike = diff(c, i) == diff(c, k);
+            if (alike) {
+                follows[i] = k;
+                break;
+            }
+        }
+        if (follows[i] == TINIT_WORDS) {
+            follows[i] = i;
+            cols.push_back(i);
         }
     }
-    a.ncols = (uint32_t)src.size();
+    src = wide;
+    src.insert(src.end(), narrow.begin(), narrow.end());
+    a.n32 = (uint32_t)wide.size();
+    a.row = a.n32 + (uint32_t)(narrow.size() + 1) / 2;
+    for (uint32_t i = 0; i < TINIT_WORDS; ++i) {
+        a.col[i] = INIT_SAME;
+        for (size_t k = 0; k < src.size(); ++k)
+            if (src[k] == follows[i]) a.col[i] = (uint8_t)k;
+    }
 }
 
 // Tensors of fewer tiles than a 256th of all, a probe block's share.
@@ -706,16 +738,23 @@ hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, b
     if (extra.p && extra.words) z.z[z.n++] = extra;
     InitArgs a;
     memset(&a, 0, sizeof a);
-    std::vector<uint32_t> src;  // the descriptor word that each column follows
+    std::vector<uint32_t> src;
     init_columns(t, a, src);
-    const size_t per = a.ncols ? INIT_DATA / a.ncols : t.size();
+    const size_t per = a.row ? INIT_DATA / a.row : t.size();
     const uint32_t *base = (const uint32_t *)&a.base;
     for (size_t f = 0; f < t.size(); f += per) {
         a.first = (uint32_t)f;
         a.count = (uint32_t)std::min<size_t>(per, t.size() - f);
-        uint32_t *p = a.data;
-        for (uint32_t c = 0; c < a.count; ++c)
-            for (uint32_t i : src) *p++ = ((const uint32_t *)&t[f + c])[i] - base[i];
+        for (uint32_t c = 0; c < a.count; ++c) {
+            uint32_t *row = a.data + c * a.row;
+            for (uint32_t k = 0; k < src.size(); ++k) {
+                const uint32_t x = ((const uint32_t *)&t[f + c])[src[k]] - base[src[k]];
+                if (k < a.n32)
+                    row[k] = x;
+                else
+                    ((int16_t *)(row + a.n32))[k - a.n32] = (int16_t)x;
+            }
+        }
         hipError_t e = launch_init(w, a, z, s);
         if (e != hipSuccess) return e;
         z.n = 0;  // cleared once
@@ -803,7 +842,7 @@ dr_status encode_back(Encode &e, hipStream_t s) {
     const Work &w = e.w;
     DR_HIP(launch_sort(w, (uint32_t)p.carve.ntiles, s));
     if (p.segment) DR_HIP(launch_segment(w, p.seg_grid_req, p.seg_block_pass, s));
-    DR_HIP(launch_fit(w, (uint32_t)p.carve.fit_blocks, p.carve.vals_est, p.dexp, s));
+    DR_HIP(launch_fit(w, (uint32_t)p.carve.fit_blocks, (uint32_t)p.carve.fit_runs, p.carve.vals_est, p.dexp, s));
     return DR_OK;
 }
 
@@ -1618,8 +1657,8 @@ dr_status dr_curvefit_encode(const float *vals, const uint64_t *n, uint64_t n_ca
     in.coef = coef_out;
     in.coef_stride = degree + 1;
     in.sigma = sigma_out;
-    in.fit_blk0 = 0;
-    p.carve.fit_blocks = (uint64_t)n_seg * FIT_CHUNKS;
+    in.fch = fit_blocks_per_run(ceil_div(n_cap, runs_cap(n_cap, degree, n_seg)), DR_FIT_POLY);
+    p.carve.fit_blocks = (uint64_t)n_seg * in.fch;
     plan_bucket_sort(p, {n_cap}, true);
     p.carve.plan();
     if (ws_bytes < p.carve.bytes && p.carve.bs_pairs) {  // no room for the buckets: the radix sort
@@ -1636,7 +1675,7 @@ dr_status dr_curvefit_encode(const float *vals, const uint64_t *n, uint64_t n_ca
     DR_HIP(launch_keygen(w, vals, n, n_cap, flags_out, persist_grid(4), s));
     DR_HIP(launch_value_setup(w, false, nullptr, s));
     DR_HIP(launch_sort(w, (uint32_t)p.carve.ntiles, s));
-    DR_HIP(launch_fit(w, (uint32_t)p.carve.fit_blocks, p.carve.vals_est, p.dexp, s));
+    DR_HIP(launch_fit(w, (uint32_t)p.carve.fit_blocks, n_seg, p.carve.vals_est, p.dexp, s));
     return DR_OK;
 }
 

@@ -29,27 +29,11 @@ namespace dr {
 // a list of indices (chunk c is items [c * bl_chunk, (c+1) * bl_chunk)).
 
 __device__ __forceinline__ uint32_t tensor_of_chunk(const Work &w, uint32_t c) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (w.td[mid].in.bl_chunk0 <= c)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.bl_chunk0 <= c; });
 }
 
 __device__ __forceinline__ uint32_t tensor_of_slice(const Work &w, uint32_t s) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (w.td[mid].in.bl_slice0 <= s)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.bl_slice0 <= s; });
 }
 
 // Calls f(index) for every item of chunk c of tensor td (strided over the
@@ -401,27 +385,11 @@ __global__ __launch_bounds__(BL_THREADS) void k_bloom_fill(Work w, uint32_t r, u
 constexpr uint32_t DIR_THREADS = 1024;
 
 __device__ __forceinline__ uint32_t tensor_of_dir_block(const Work &w, uint32_t b) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (w.td[mid].in.dir_blk0 <= b)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.dir_blk0 <= b; });
 }
 
 __device__ __forceinline__ uint32_t tensor_of_dir_slice(const Work &w, uint32_t s) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (w.td[mid].in.dir_sl0 <= s)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.dir_sl0 <= s; });
 }
 
 template <bool FROM_BITMAP>

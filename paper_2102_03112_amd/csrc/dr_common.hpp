@@ -83,7 +83,8 @@ constexpr uint32_t BS_CAP = 4096;
 constexpr uint32_t BS_AVG = 1024;
 constexpr uint32_t BS_OVER = 16;
 constexpr uint32_t BS_MAX_BUCKETS = 512;
-constexpr uint32_t FIT_CHUNKS = 8;            // partial-moment blocks per fitted run
+constexpr uint32_t FIT_CHUNKS = 8;            // partial-moment blocks per fitted run (at most)
+constexpr uint32_t FIT_MIN_CHUNK = 2048;       // fewest values per such block (but of a shorter run)
 constexpr uint32_t MAX_DEG = 7;
 constexpr uint32_t MAX_SEG = 4096;            // most runs per tensor
 // index policies (Section 4; Sections 10.4, 10.5)
@@ -128,7 +129,9 @@ struct TInit {
     uint32_t degree;     // requested polynomial degree
     uint32_t nseg;       // requested runs
     uint32_t m_words_in; // filter words fixed by the caller, or 0: derive from n
-    uint32_t fit_blk0;   // first block of this tensor in the fit grid
+    uint32_t fit_blk0;   // first block of this tensor in the fit grid: fch blocks per run
+    uint32_t fit_run0;   // first run of this tensor over all tensors
+    uint32_t fch;        // partial-moment blocks per run
     uint32_t bl_chunk;   // Bloom insert: bitmap tiles (from the bitmap) or items (from a list) per chunk
     uint32_t bl_chunk0;  // first Bloom chunk of this tensor
     uint32_t bl_nchunks; // Bloom chunks reserved for this tensor
@@ -286,7 +289,6 @@ struct Work {
     uint32_t bstotal;         // buckets reserved over all tensors (0: the radix sort)
     uint32_t bsmulti;         // some tensor may have several
     double *fit_part;         // fit: partial moments
-    uint32_t fit_runs;
     uint32_t *bpos;           // Bloom insert: bucketed in-slice positions
     uint32_t *btab;           // Bloom insert: per (slice, chunk) counts, then offsets within the slice
     uint32_t *brow;           // Bloom insert: per reserved slice, its count; brow + bslices: its start
@@ -588,6 +590,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_view(const void *p, uin
 
 __device__ __forceinline__ uint32_t buffer_u32(__amdgpu_buffer_rsrc_t v, uint32_t byte_off) {
     return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(v, byte_off, 0, 0);
+}
+
+// The last tensor t < n whose start is at or below a value, `le(t)` telling
+// whether t's is (starts ascend, and tensor 0's always is): each wave of the
+// block searches 64 ways at a time, so 161 tensors take two dependent reads
+// instead of eight.  Every lane must call it, with the same arguments.
+template <typename F>
+__device__ __forceinline__ uint32_t last_tensor(uint32_t n, F le) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lo = 0;
+    for (uint32_t span = n; span > 1;) {
+        const uint32_t step = (span + 63u) / 64u, off = lane * step;
+        const uint32_t i = popc64(ballot(off < span && (off == 0 || le(lo + off)))) - 1u;
+        lo += i * step;
+        span = min(step, span - i * step);
+    }
+    return lo;
 }
 
 // tensor holding global tile `tile` (one read of the table k_init fills)

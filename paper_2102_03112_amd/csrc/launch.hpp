@@ -35,18 +35,19 @@ void trace_mark(hipStream_t s, const char *kernel);
 
 // Descriptors as k_init's arguments carry them: the call's first tensor
 // whole, and of the others only the words that differ, as columns of
-// differences from it (words that differ alike share a column).  A launch
-// takes INIT_DATA / ncols tensors, where whole descriptors gave 14: for 161
-// tensors of mixed sizes two launches for a receiver and four for a sender
-// instead of twelve, about 5 us each.
+// differences from it (words that differ alike share a column, one within 16
+// bits takes half a word).  A launch takes INIT_DATA / row tensors, where
+// whole descriptors gave 14: for 161 tensors of mixed sizes two launches for
+// a receiver and three for a sender instead of twelve, about 5 us each.
 constexpr uint32_t TINIT_WORDS = sizeof(TInit) / 4;
 constexpr uint32_t INIT_DATA = 768;
 constexpr uint8_t INIT_SAME = 0xff;  // a word without a column
 struct InitArgs {
-    uint32_t first, count, ncols;
+    uint32_t first, count;
+    uint32_t n32, row;  // columns of whole words; words per tensor
     TInit base;
-    uint8_t col[TINIT_WORDS];
-    uint32_t data[INIT_DATA];  // tensor first + c: [c * ncols, (c + 1) * ncols)
+    uint8_t col[TINIT_WORDS];  // column k: word k (k < n32), or half-word k - n32 after those
+    uint32_t data[INIT_DATA];  // tensor first + c: [c row, (c + 1) row)
 };
 static_assert(INIT_DATA >= TINIT_WORDS && TINIT_WORDS < INIT_SAME, "any tensor fits a launch");
 
@@ -118,7 +119,8 @@ hipError_t launch_sort(const Work &w, uint32_t cap_tiles, hipStream_t s);
 hipError_t launch_segment(const Work &w, uint32_t grid_req, bool block_pass, hipStream_t s);
 // the fit's moments with the packing of the reorder maps (one launch), the
 // solve, then the double-exponential passes if any tensor asks for them
-hipError_t launch_fit(const Work &w, uint32_t fit_blocks, uint64_t vals_est, bool dexp, hipStream_t s);
+hipError_t launch_fit(const Work &w, uint32_t fit_blocks, uint32_t fit_runs, uint64_t vals_est, bool dexp,
+                      hipStream_t s);
 hipError_t launch_curvefit_decode(const Work &w, const float *coef, const uint32_t *sigma, const uint64_t *n,
                                   uint64_t n_cap, float *vals_out, uint64_t *flags_out, int grid_persist,
                                   hipStream_t s);

@@ -23,8 +23,10 @@ namespace dr {
 
 // Word i of the descriptor of the launch's tensor c.
 __device__ __forceinline__ uint32_t init_word(const InitArgs &a, uint32_t c, uint32_t i) {
-    const uint32_t k = a.col[i];
-    return ((const uint32_t *)&a.base)[i] + (k == INIT_SAME ? 0u : a.data[c * a.ncols + k]);
+    const uint32_t k = a.col[i], base = ((const uint32_t *)&a.base)[i];
+    if (k == INIT_SAME) return base;
+    const uint32_t *row = a.data + c * a.row;
+    return base + (k < a.n32 ? row[k] : (uint32_t)(int32_t)((const int16_t *)(row + a.n32))[k - a.n32]);
 }
 
 // Set-up: the blocks write the tensor descriptors of this launch, a word per
@@ -84,14 +86,8 @@ hipError_t launch_init(const Work &w, const InitArgs &a, const ZeroArgs &z, hipS
 // tensors
 template <int PHASE>
 __device__ __forceinline__ int tensor_of_hist_block(const Work &w, uint32_t b) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if ((PHASE == 0 ? w.td[mid].in.hb0 : w.td[mid].in.rb0) <= b)
-            lo = mid;
-        else
-            hi = mid;
-    }
+    const uint32_t lo =
+        last_tensor(w.ntensors, [&](uint32_t t) { return (PHASE == 0 ? w.td[t].in.hb0 : w.td[t].in.rb0) <= b; });
     const TInit &in = w.td[lo].in;
     const uint32_t b0 = PHASE == 0 ? in.hb0 : in.rb0, bn = PHASE == 0 ? in.hbn : in.rbn;
     if (bn == 0 || b < b0 || b >= b0 + bn) return -1;

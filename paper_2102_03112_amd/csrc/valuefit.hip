@@ -60,15 +60,7 @@ hipError_t launch_value_setup(const Work &w, bool payload, uint64_t *counts_out,
 // LSD radix sort, segmented by tensor
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t tensor_of_stile(const Work &w, uint32_t g) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (w.td[mid].stile0 <= g)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].stile0 <= g; });
 }
 
 // Before the passes: each tensor's totals of all four digits, and the
@@ -649,14 +641,7 @@ __global__ __launch_bounds__(BS_THREADS) void k_bsort_bucket(Work w) {
     __shared__ BsLds<BS_THREADS, BS_CAP> l;
     constexpr uint32_t E = BS_CAP / BS_THREADS;
     static_assert(BS_MAX_BUCKETS <= BS_THREADS, "a count per thread");
-    // the tensor of this bucket: a 64-way search, each wave for itself
-    uint32_t lo = 0;
-    for (uint32_t span = w.ntensors; span > 1;) {
-        const uint32_t step = (span + 63u) / 64u, t = lo + (threadIdx.x & 63u) * step;
-        const uint64_t le = ballot(t < w.ntensors && (threadIdx.x & 63u) * step < span && w.td[t].in.bs0 <= blockIdx.x);
-        lo += (popc64(le) - 1u) * step;  // lane 0 is always among them
-        span = min(step, w.ntensors - lo);
-    }
+    const uint32_t lo = last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.bs0 <= blockIdx.x; });
     const TDesc &td = w.td[lo];
     const uint32_t nv = td.nv, B = bs_buckets(td, nv), b = blockIdx.x - td.in.bs0;
     if (b >= B || nv == 0) return;
@@ -1284,15 +1269,11 @@ __device__ __forceinline__ void run_range(const Work &w, const TDesc &td, uint32
     }
 }
 __device__ __forceinline__ uint32_t tensor_of_fit_block(const Work &w, uint32_t b) {
-    uint32_t lo = 0, hi = w.ntensors;
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (w.td[mid].in.fit_blk0 <= b)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.fit_blk0 <= b; });
+}
+
+__device__ __forceinline__ uint32_t tensor_of_run(const Work &w, uint32_t r) {
+    return last_tensor(w.ntensors, [&](uint32_t t) { return w.td[t].in.fit_run0 <= r; });
 }
 
 // Moments of one chunk of a run: sums of t^e (e <= 2D) and t^e y (e <= D)
@@ -1311,11 +1292,14 @@ constexpr uint32_t FIT_BATCH = 8;
 // Chunks a run of ns points is cut into: at most FIT_CHUNKS, each at least
 // a batch per thread.  A block reduces its 3 D + 2 sums over all its waves
 // whatever its chunk's size, so many chunks of a short run would be mostly
-// reductions.  The blocks of unused chunks write zero partials.
-constexpr uint64_t FIT_MIN_CHUNK = (uint64_t)FIT_THREADS * FIT_BATCH;
-__device__ __forceinline__ uint32_t fit_chunks(uint64_t ns) {
+// reductions.  The plan gives a tensor fch blocks per run, as many as its
+// expected values need; the blocks of unused chunks write zero partials.
+// (With FIT_CHUNKS blocks for every run, 161 layers of 25.6 M elements
+// launched 10,304 blocks, most of them idle: FITLAYERS.)
+static_assert(FIT_MIN_CHUNK == FIT_THREADS * FIT_BATCH, "a batch per thread");
+__device__ __forceinline__ uint32_t fit_chunks(uint64_t ns, uint32_t most) {
     const uint64_t c = (ns + FIT_MIN_CHUNK - 1) / FIT_MIN_CHUNK;
-    return (uint32_t)(c < 1 ? 1 : (c > FIT_CHUNKS ? FIT_CHUNKS : c));
+    return (uint32_t)(c < 1 ? 1 : (c > most ? most : c));
 }
 
 template <int D>
@@ -1375,10 +1359,20 @@ __device__ void fit_moments_body(const float *y, uint64_t lo_run, uint64_t ns, u
 
 __device__ void solve_run(const TDesc &td, uint32_t s, const double *mom);
 
+// Caller-owned coefficient rows past the fitted runs are zeroed.
+__device__ __forceinline__ void zero_coef_row(const TDesc &td, uint32_t s) {
+    if (td.in.coef && s < td.in.nseg && threadIdx.x < td.in.coef_stride)
+        td.in.coef[(uint64_t)s * td.in.coef_stride + threadIdx.x] = 0.0f;
+}
+
 __device__ void pack_sigma_words(const Work &w, uint32_t first, uint32_t stride);
 
 // Moments of one chunk of one run (blocks [0, fit_blocks)); the blocks
 // after them pack the reorder map, which needs only the sort.
+// SOLVE: every run of the call has one block, which solves it as well (one
+// launch less; in the other form the solve's registers would cost the sums
+// their occupancy: resnet50_25m 27 -> 45 us).
+template <bool SOLVE>
 __global__ __launch_bounds__(FIT_THREADS) void k_fit_moments(Work w, uint32_t fit_blocks) {
     if (blockIdx.x >= fit_blocks) {
         pack_sigma_words(w, (blockIdx.x - fit_blocks) * FIT_THREADS + threadIdx.x,
@@ -1388,13 +1382,18 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_moments(Work w, uint32_t fi
     const uint32_t t = tensor_of_fit_block(w, blockIdx.x);
     const TDesc &td = w.td[t];
     const uint32_t local = blockIdx.x - td.in.fit_blk0;
-    const uint32_t s = local / FIT_CHUNKS, ch = local % FIT_CHUNKS;
-    if (s >= td.seff || td.model == FIT_DEXP) return;
+    const uint32_t fch = td.in.fch, s = local / fch, ch = local % fch;
+    if (s >= td.seff) {
+        if (SOLVE) zero_coef_row(td, s);
+        return;
+    }
+    if (td.model == FIT_DEXP) return;
     uint64_t lo, hi;
     run_range(w, td, s, &lo, &hi);
     const uint64_t ns = hi - lo;
-    const uint32_t nch = fit_chunks(ns);
-    double *out = w.fit_part + (uint64_t)blockIdx.x * NMOM;
+    const uint32_t nch = fit_chunks(ns, fch);
+    __shared__ double mom[SOLVE ? NMOM : 1];
+    double *out = SOLVE ? mom : w.fit_part + (uint64_t)blockIdx.x * NMOM;
     if (ch >= nch) {  // block-uniform: the run has fewer chunks; this one adds nothing
         if (threadIdx.x < NMOM) out[threadIdx.x] = 0.0;
         return;
@@ -1411,19 +1410,21 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_moments(Work w, uint32_t fi
         case 6: fit_moments_body<6>(y, lo, ns, j0, j1, out); break;
         default: fit_moments_body<7>(y, lo, ns, j0, j1, out); break;
     }
+    if (SOLVE) {
+        __syncthreads();
+        if (threadIdx.x == 0) solve_run(td, s, mom);
+    }
 }
 
 // One run per block: its chunks' moments summed in chunk order, then the
 // solve (one thread; the system is at most 8 x 8).  Caller-owned
 // coefficient rows past the fitted runs are zeroed.
 __global__ __launch_bounds__(64) void k_fit_solve(Work w) {
-    const uint32_t blk = blockIdx.x * FIT_CHUNKS;
-    const uint32_t t = tensor_of_fit_block(w, blk);
+    const uint32_t t = tensor_of_run(w, blockIdx.x);
     const TDesc &td = w.td[t];
-    const uint32_t s = (blk - td.in.fit_blk0) / FIT_CHUNKS;
+    const uint32_t fch = td.in.fch, s = blockIdx.x - td.in.fit_run0;
     if (s >= td.seff) {
-        if (td.in.coef && s < td.in.nseg && threadIdx.x < td.in.coef_stride)
-            td.in.coef[(uint64_t)s * td.in.coef_stride + threadIdx.x] = 0.0f;
+        zero_coef_row(td, s);
         return;
     }
     if (td.model == FIT_DEXP) {  // fitted by k_dexp_pass: its state starts cleared
@@ -1433,9 +1434,12 @@ __global__ __launch_bounds__(64) void k_fit_solve(Work w) {
     }
     __shared__ double mom[NMOM];
     if (threadIdx.x < NMOM) {
-        const double *part = w.fit_part + (uint64_t)blk * NMOM;
-        double acc = 0.0;
-        for (uint32_t c = 0; c < FIT_CHUNKS; ++c) acc += part[c * NMOM + threadIdx.x];
+        const double *part = w.fit_part + ((uint64_t)td.in.fit_blk0 + (uint64_t)s * fch) * NMOM;
+        double v[FIT_CHUNKS], acc = 0.0;
+#pragma unroll
+        for (uint32_t c = 0; c < FIT_CHUNKS; ++c) v[c] = c < fch ? part[c * NMOM + threadIdx.x] : 0.0;
+#pragma unroll
+        for (uint32_t c = 0; c < FIT_CHUNKS; ++c) acc += v[c];
         mom[threadIdx.x] = acc;
     }
     __syncthreads();
@@ -1680,10 +1684,9 @@ __device__ void dexp_part_sums(const float *y, uint64_t ns, uint32_t part, bool 
 // 2 + DEXP_ITERS times; a run whose fit has ended returns at once.
 __global__ __launch_bounds__(DEXP_THREADS) void k_dexp_pass(Work w, uint32_t pass) {
     const uint32_t run = blockIdx.x / DEXP_PARTS, part = blockIdx.x % DEXP_PARTS;
-    const uint32_t blk = run * FIT_CHUNKS;
-    const uint32_t t = tensor_of_fit_block(w, blk);
+    const uint32_t t = tensor_of_run(w, run);
     const TDesc &td = w.td[t];
-    const uint32_t s = (blk - td.in.fit_blk0) / FIT_CHUNKS;
+    const uint32_t s = run - td.in.fit_run0;
     if (td.model != FIT_DEXP || s >= td.seff) return;
     DexpState &st = *dexp_state(w, run);
     if (st.done) return;
@@ -1698,7 +1701,7 @@ __global__ __launch_bounds__(DEXP_THREADS) void k_dexp_pass(Work w, uint32_t pas
 #pragma unroll
     for (int p = 0; p < 4; ++p) th[p] = st.tt[p];
     dexp_part_sums(y, ns, part, pass == 0, th, red, tot);
-    double *parts = w.fit_part + (uint64_t)blk * NMOM;  // DEXP_PARTS x 15 sums
+    double *parts = w.fit_part + (uint64_t)run * FIT_CHUNKS * NMOM;  // DEXP_PARTS x 15 sums
     if (threadIdx.x < 15) parts[part * 15 + threadIdx.x] = tot[threadIdx.x];
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1801,7 +1804,8 @@ __global__ __launch_bounds__(DEXP_THREADS) void k_dexp_pass(Work w, uint32_t pas
     }
 }
 
-hipError_t launch_fit(const Work &w, uint32_t fit_blocks, uint64_t vals_est, bool dexp, hipStream_t s) {
+hipError_t launch_fit(const Work &w, uint32_t fit_blocks, uint32_t fit_runs, uint64_t vals_est, bool dexp,
+                      hipStream_t s) {
     // the fit's chunk blocks, then blocks packing the reorder maps: one per
     // PACK_PER_BLOCK of the values the plan expects (each takes at most 32
     // bits, so as many words), at least 8 and at most 512.  Sized by the
@@ -1813,14 +1817,18 @@ hipError_t launch_fit(const Work &w, uint32_t fit_blocks, uint64_t vals_est, boo
     constexpr uint64_t PACK_PER_BLOCK = 4ull * FIT_THREADS;
     const uint32_t pack_blocks =
         (uint32_t)std::min<uint64_t>(512, std::max<uint64_t>(8, (vals_est + PACK_PER_BLOCK - 1) / PACK_PER_BLOCK));
-    k_fit_moments<<<fit_blocks + pack_blocks, FIT_THREADS, 0, s>>>(w, fit_blocks);
+    if (fit_blocks == fit_runs && !dexp) {  // one block per run (or no run)
+        k_fit_moments<true><<<fit_blocks + pack_blocks, FIT_THREADS, 0, s>>>(w, fit_blocks);
+        trace_mark(s, "k_fit_moments");
+        return hipGetLastError();
+    }
+    k_fit_moments<false><<<fit_blocks + pack_blocks, FIT_THREADS, 0, s>>>(w, fit_blocks);
     trace_mark(s, "k_fit_moments");
-    if (fit_blocks == 0) return hipGetLastError();
-    k_fit_solve<<<fit_blocks / FIT_CHUNKS, 64, 0, s>>>(w);
+    k_fit_solve<<<fit_runs, 64, 0, s>>>(w);
     trace_mark(s, "k_fit_solve");
     if (dexp) {
         for (uint32_t pass = 0; pass < 2u + (uint32_t)DEXP_ITERS; ++pass) {
-            k_dexp_pass<<<(fit_blocks / FIT_CHUNKS) * DEXP_PARTS, DEXP_THREADS, 0, s>>>(w, pass);
+            k_dexp_pass<<<fit_runs * DEXP_PARTS, DEXP_THREADS, 0, s>>>(w, pass);
             trace_mark(s, "k_dexp_pass");
         }
     }
