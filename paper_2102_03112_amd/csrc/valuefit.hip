@@ -409,7 +409,7 @@ __device__ __forceinline__ void bs_place(const uint64_t (&x)[E], uint32_t (&at)[
 }
 
 // The pairs out[0..n) in order in place, n at most E NT, by the whole block;
-// h: BS_L1 + 1 words.  For a bin that bs_sort_lds found too full: bins over
+// h: BS_L1 + 1 words, spare: E NT / BS_BIN_MAX + 1.  For a bin that bs_sort_lds found too full: bins over
 // the bin's own range (values that repeat differ in their numbers, which are
 // evenly spread), and where that leaves one too full, a bitonic network whose
 // comparisons all ascend (a merge's first step pairs mirror images), so that
@@ -471,7 +471,9 @@ struct BsLds {
     uint64_t out[CAP];
     uint64_t lohi[2 * NT / 64];
     uint32_t h1[BS_L1 + 1], h2[CAP + 1];
-    uint32_t heavy[CAP / BS_BIN_MAX + 1], spare[BS_L1 / BS_BIN_MAX + 1];
+    // a listed bin holds more than BS_BIN_MAX of at most CAP pairs, also in
+    // the lists of bs_sort_bin, whose bin may be all of them
+    uint32_t heavy[CAP / BS_BIN_MAX + 1], spare[CAP / BS_BIN_MAX + 1];
     uint32_t scratch[NT / 64 + 1];
 };
 

@@ -41,13 +41,18 @@ def values(kind, n, rng):
         v = 2.0 + rng.random(n)
         v[sample_places(n)] = 1.0
         return v
+    if kind == "ulps":  # 30 neighbouring floats, each many times, and two far off: one bin cut into 30 too full ones
+        v = (np.float32(1.5).view(np.int32) + rng.integers(0, 30, n, dtype=np.int32)).view(np.float32)
+        v[[0, n // 2]] = 1e30, -1e30
+        return v
     if kind == "wide":  # both ends of the range of floats
         return rng.standard_normal(n) * 10.0 ** rng.integers(-40, 38, n)
     raise ValueError(kind)
 
 
 SIZES = [1, 2, 63, 513, CAP - 1, CAP, CAP + 1, 8191, 20_000, 100_001, 512 * AVG, 512 * AVG + 1]
-CASES = [(n, "normal") for n in SIZES] + [(n, k) for n in (CAP, 30_000) for k in ("equal", "zeros", "coarse", "sorted", "wide")]
+CASES = [(n, "normal") for n in SIZES] + [(n, "ulps") for n in (CAP, 30_000, 512 * AVG)]
+CASES += [(n, k) for n in (CAP, 30_000) for k in ("equal", "zeros", "coarse", "sorted", "wide")]
 
 
 @pytest.mark.parametrize("n,kind", CASES + [(30_000, "outgrown")])
