@@ -94,14 +94,14 @@ struct Carve {
     // false positives; d for the support): sizes the reorder-map packing grid
     uint64_t vals_est = 0;
     // bucket sort: buckets reserved, whether some tensor may have several,
-    // and pairs of its own (the round trip's lie in the selection's arrays)
+    // and the pairs of a plan that may need more than 2 per slot
     uint64_t bs_total = 0, bs_pairs = 0;
     bool bs_multi = false;
     bool query_only = false;  // descriptors, tile counts, the positives bitmap and the tile table only
     size_t bytes = 0;
-    size_t o_td, o_glob, o_pstat, o_histA, o_shist, o_fcnt, o_tcnt, o_toff, o_ccnt, o_hist, o_sel, o_pbits, o_ckey, o_cidx, o_S, o_P,
-        o_V, o_sstat, o_sdig, o_ttab, o_fit, o_btab, o_brow, o_keyA, o_keyB, o_valA, o_valB, o_sig, o_vs, o_bnd,
-        o_segst, o_segpart, o_bscnt, o_bsspl, o_bspair, o_qlist, o_qbkt, o_qtab, o_qrow;
+    size_t o_td, o_glob, o_pstat, o_histA, o_shist, o_fcnt, o_tcnt, o_toff, o_ccnt, o_hist, o_sel, o_pbits, o_ckey, o_cidx, o_S, o_subk,
+        o_sstat, o_sdig, o_ttab, o_fit, o_btab, o_brow, o_keyA, o_keyB, o_valA, o_valB, o_sig, o_vs, o_bnd,
+        o_segst, o_segpart, o_bscnt, o_bsspl, o_qlist, o_qbkt, o_qtab, o_qrow;
 
     void plan() {
         size_t at = 0;
@@ -132,8 +132,9 @@ struct Carve {
         o_ckey = take(all * 4 * slots);
         o_cidx = take(all * 4 * slots);
         o_S = take(all * 4 * slots);
-        o_P = take(all * 4 * slots);
-        o_V = take(all * 4 * slots);
+        // the bucket sort's pairs take the selection's four arrays, which it no
+        // longer needs: 2 pairs per slot, and what a plan of its own needs more
+        o_subk = take(all * std::max<uint64_t>(4 * slots, 8 * bs_pairs > 12 * slots ? 8 * bs_pairs - 12 * slots : 0));
         o_sstat = take(all * 8ull * 4 * SORT_BINS * ntiles);
         o_sdig = take(all * 4ull * 4 * SORT_BINS * ntensors);
         o_fit = take(all * 8ull * NMOM * fit_blocks);
@@ -144,9 +145,6 @@ struct Carve {
         o_segpart = take(all * sizeof(SegPart) * SEG_GRID_BLOCKS * segslots);
         o_bscnt = take(all * 4 * bs_total);
         o_bsspl = take(all * 8 * bs_total);
-        // after the selection its candidates, index lists and value copy are
-        // free: 2.5 pairs per slot
-        o_bspair = bs_pairs ? take(all * 8 * bs_pairs) : o_ckey;
         o_keyA = take(all * 4 * slots);
         o_keyB = take(all * 4 * slots);
         o_valA = take(all * 4 * slots);
@@ -176,10 +174,8 @@ struct Carve {
         w.shist = (uint32_t *)(ws + o_shist);
         w.fcnt = (uint32_t *)(ws + o_fcnt);
         w.S = (uint32_t *)(ws + o_S);
-        w.P = (uint32_t *)(ws + o_P);
-        w.V = (float *)(ws + o_V);
-        w.sub_key = (uint32_t *)(ws + o_P);  // short list of the top-r select, before P exists
-        w.sub_idx = (uint32_t *)(ws + o_V);
+        w.sub_key = (uint32_t *)(ws + o_subk);
+        w.sub_idx = (uint32_t *)(ws + o_keyA);  // before the value path needs it
         w.sstat = (uint64_t *)(ws + o_sstat);
         w.sdig = (uint32_t *)(ws + o_sdig);
         w.tile_tensor = (uint32_t *)(ws + o_ttab);
@@ -199,7 +195,7 @@ struct Carve {
         w.segpart = (SegPart *)(ws + o_segpart);
         w.bscnt = (uint32_t *)(ws + o_bscnt);
         w.bsspl = (uint64_t *)(ws + o_bsspl);
-        w.bspair = (uint64_t *)(ws + o_bspair);
+        w.bspair = (uint64_t *)(ws + o_ckey);
         w.bstotal = (uint32_t)bs_total;
         w.bsmulti = bs_multi ? 1u : 0u;
         w.qlist = (uint32_t *)(ws + o_qlist);
@@ -254,7 +250,6 @@ void plan_topr_hist(TInit &in, uint64_t d, uint64_t r, uint64_t ht, bool sample,
         uint64_t hi = std::min<uint64_t>(nsamp, (uint64_t)std::ceil(rho + delta));
         if (lo > hi) lo = hi;
         in.srate = (uint32_t)rate;
-        in.nsamp = (uint32_t)nsamp;
         in.slo = (uint32_t)lo;
         in.shi = (uint32_t)hi;
         in.hbn = (uint32_t)ceil_div(ns, SAMPLE_SEGS_PER_BLOCK);
@@ -435,7 +430,7 @@ void plan_bucket_sort(Plan &p, const std::vector<uint64_t> &most, bool own_pairs
     uint32_t at = 0;
     for (size_t t = 0; t < most.size(); ++t) {
         p.t[t].bs0 = at;
-        p.t[t].bsn = n[t];
+        p.t[t].bsn = (uint16_t)n[t];
         at += n[t];
     }
     p.carve.bs_total = total;
@@ -618,7 +613,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
         const bool even = cfg->segmentation == DR_SEG_EQUAL && cfg->n_seg >= 1;
         in.fit_run0 = (uint32_t)fit_runs;
         in.fit_blk0 = (uint32_t)fit_blocks;
-        in.fch = fit_blocks_per_run(even ? ceil_div(most[t], runs_cap(most[t], degree, cfg->n_seg)) : most[t],
+        in.fch = (uint16_t)fit_blocks_per_run(even ? ceil_div(most[t], runs_cap(most[t], degree, cfg->n_seg)) : most[t],
                                     cfg->fit_model);
         fit_runs += runs;
         fit_blocks += runs * in.fch;
@@ -799,7 +794,6 @@ dr_status encode_prepare(const float *g, const dr_config *cfg, uint8_t *payload,
     if (!ws_ok(ws, ws_bytes, e.p.carve.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", e.p.carve.bytes);
     for (size_t t = 0; t < e.p.t.size(); ++t) {
-        e.p.t[t].rec_off = e.rec_off[t];
         e.p.t[t].rec_cap = e.rec_off[t + 1] - e.rec_off[t];
         e.p.t[t].rec = payload + e.rec_off[t];
         e.p.t[t].bits = (uint32_t *)(payload + e.rec_off[t] + HDR_BYTES);
@@ -880,7 +874,6 @@ dr_status decode_prepare(const uint8_t *payload, const dr_config *cfg, float *de
     if (!ws_ok(ws, ws_bytes, dd.p.carve.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", dd.p.carve.bytes);
     for (size_t t = 0; t < dd.p.t.size(); ++t) {
-        dd.p.t[t].rec_off = dd.rec_off[t];
         dd.p.t[t].rec_cap = dd.rec_off[t + 1] - dd.rec_off[t];
         dd.p.t[t].rec = const_cast<uint8_t *>(payload) + dd.rec_off[t];
         dd.p.t[t] = receiver_init(dd.p.t[t]);
@@ -1142,7 +1135,6 @@ dr_status decode_sum_impl(const uint8_t *const *payloads, uint32_t npay, const d
             TInit in = p.t[t];
             in.tile0 = (uint32_t)(q * ntiles1 + in.tile0);
             in.slot = q * ntiles1 * TILE + in.slot;
-            in.rec_off = rec_off[t];
             in.rec_cap = rec_off[t + 1] - rec_off[t];
             in.rec = const_cast<uint8_t *>(payloads[q]) + rec_off[t];
             vt.push_back(receiver_init(in));
@@ -1330,7 +1322,7 @@ void check_bucket_sort(const Plan &p, RangeCheck &rc) {
         at += in.bsn;
     }
     rc.fail_if(at != c.bs_total, "%llu buckets of %llu", (unsigned long long)at, (unsigned long long)c.bs_total);
-    rc.fail_if(c.o_bspair + 16 * c.slots > c.o_V, "the buckets' pairs end past the selection's arrays");
+    rc.fail_if(c.o_ckey + 16 * c.slots > c.o_sstat, "the buckets' pairs end past the selection's arrays");
 }
 
 dr_status check_ranges_impl(const dr_config *cfg, uint64_t *violations) {
@@ -1657,7 +1649,7 @@ dr_status dr_curvefit_encode(const float *vals, const uint64_t *n, uint64_t n_ca
     in.coef = coef_out;
     in.coef_stride = degree + 1;
     in.sigma = sigma_out;
-    in.fch = fit_blocks_per_run(ceil_div(n_cap, runs_cap(n_cap, degree, n_seg)), DR_FIT_POLY);
+    in.fch = (uint16_t)fit_blocks_per_run(ceil_div(n_cap, runs_cap(n_cap, degree, n_seg)), DR_FIT_POLY);
     p.carve.fit_blocks = (uint64_t)n_seg * in.fch;
     plan_bucket_sort(p, {n_cap}, true);
     p.carve.plan();

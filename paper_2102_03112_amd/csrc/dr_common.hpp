@@ -112,7 +112,6 @@ constexpr uint32_t HDR_MAGIC = 0x31435244u;   // "DRC1"
 // Static per-tensor set-up, written by the host (through kernel arguments).
 struct TInit {
     uint64_t off;        // first element of the tensor in g / dense_out
-    uint64_t rec_off;    // byte offset of the tensor's payload record
     uint64_t slot;       // first element of the tensor's padded slot (= tile0 * TILE)
     uint64_t bl_pos0;    // first entry of this tensor in the Bloom position buffer
     uint64_t bl_tab0;    // first entry of this tensor in the Bloom count table
@@ -130,8 +129,6 @@ struct TInit {
     uint32_t nseg;       // requested runs
     uint32_t m_words_in; // filter words fixed by the caller, or 0: derive from n
     uint32_t fit_blk0;   // first block of this tensor in the fit grid: fch blocks per run
-    uint32_t fit_run0;   // first run of this tensor over all tensors
-    uint32_t fch;        // partial-moment blocks per run
     uint32_t bl_chunk;   // Bloom insert: bitmap tiles (from the bitmap) or items (from a list) per chunk
     uint32_t bl_chunk0;  // first Bloom chunk of this tensor
     uint32_t bl_nchunks; // Bloom chunks reserved for this tensor
@@ -163,10 +160,12 @@ struct TInit {
     // sampled top-r (srate 0: the exact histogram; hb0, hbn then count the
     // sample's blocks)
     uint32_t srate;      // one sampled segment in srate (a power of 2)
-    uint32_t nsamp;      // elements in the sample
     uint32_t slo, shi;   // sample ranks that bound the bracket: rho -/+ delta
     uint32_t rb0, rbn;   // blocks of the full histogram for a redo
-    uint32_t bs0, bsn;   // bucket sort: first bucket of this tensor, buckets reserved (0: the radix sort)
+    uint32_t fit_run0;   // first run of this tensor over all tensors
+    uint32_t bs0;        // bucket sort: first bucket of this tensor
+    uint16_t bsn;        // bucket sort: buckets reserved (0: the radix sort)
+    uint16_t fch;        // partial-moment blocks per run
 };
 
 // Chord segmentation over the whole grid (at most SEG_GRID_RUNS runs per
@@ -269,11 +268,9 @@ struct Work {
     uint32_t *histA;          // top-r: per tensor, HISTA_COPIES histograms of the candidates' (bin - bL, key bits 19..10)
     uint32_t *shist;          // sampled top-r: per tensor, SHIST_COPIES first-digit histograms of the sample
     uint32_t *fcnt;           // sampled top-r: [tensor][FCNT_COPIES][FCNT_W] counts of the filter pass
-    uint32_t *sub_key;        // top-r short list (borrows P, which is written later)
-    uint32_t *sub_idx;        // top-r short list (borrows V)
+    uint32_t *sub_key;        // top-r short list (keys)
+    uint32_t *sub_idx;        // top-r short list (indices; borrows keyA, which the value path writes later)
     uint32_t *S;              // selected indices, per tensor slot
-    uint32_t *P;              // sender's positives, per tensor slot
-    float *V;                 // g[P]
     uint32_t *keyA, *keyB;    // sort keys
     uint32_t *valA, *valB;    // sort payloads
     uint64_t *sstat;          // sort look-back: (flag << 32 | count) per pass, tile and digit

@@ -125,6 +125,39 @@ def test_decode_sum_rejects_bad_arguments(L):
     assert f(one, 2, ctypes.byref(bad.c), 1.0, FAKE, None, FAKE, big, None) == B.DR_EINVAL
 
 
+# Exact scratch needs that a caller may have sized a workspace by (the error
+# message states them): (element counts, ratio, encode and decode, a sum of two
+# payloads).
+NEEDS = [
+    ([100], (1, 100), 412_928, 35_584),
+    ([36_864], (1, 100), 1_928_448, 43_776),
+    ([1_048_576], (1, 100), 48_723_712, 302_080),
+    ([200_000] * 5, (1, 2), 47_404_032, 293_888),
+    ([4_000_000, 1000, 60_000], (1, 10), 188_774_656, 1_076_736),
+    ([422_600], None, 19_932_672, 143_360),
+    ([40_000] * 161, (1, 2), 335_459_328, 1_844_480),
+]
+
+
+@pytest.mark.parametrize("sizes,ratio,enc,total", NEEDS)
+def test_workspace_needs_do_not_grow(L, sizes, ratio, enc, total):
+    cfg = _cfg(offsets=[sum(sizes[:i]) for i in range(len(sizes) + 1)], ratio=ratio)
+    two = (ctypes.c_void_p * 2)(FAKE.value, FAKE.value)
+
+    def need(call):
+        assert call(0) == B.DR_EINVAL
+        return int(re.search(r"need (\d+)", B.last_error()).group(1))
+
+    c = ctypes.byref(cfg.c)
+    e = need(lambda n: L.dr_payload_encode(FAKE, c, FAKE, 1 << 60, None, FAKE, n, None))
+    assert e <= enc
+    assert need(lambda n: L.dr_payload_decode(FAKE, c, FAKE, None, None, None, FAKE, n, None)) <= enc
+    s = need(lambda n: L.dr_payload_decode_sum(two, 2, c, 1.0, FAKE, None, FAKE, n, None))
+    assert s <= total
+    # and the round trip finds room for both sides at once
+    assert e + s <= B.workspace_bytes(cfg.d, cfg.n_tensors)
+
+
 def test_null_config_and_zero_tensors(L):
     assert L.dr_payload_layout(None, None) == 0
     cfg = _cfg()
