@@ -312,8 +312,10 @@ constexpr uint32_t BS_THREADS = 512;
 constexpr uint32_t BS_SPLIT_THREADS = 1024;
 constexpr uint32_t BS_SAMPLE = BS_OVER * BS_MAX_BUCKETS;
 constexpr uint32_t BS_L1 = 1024;       // first-level bins of the LDS sort
-constexpr uint32_t BS_BIN_MAX = 128;   // fuller second-level bins are sorted one by one (with 32, the bucket
-                                       // between the signs, two narrow clusters, took 80 us)
+constexpr uint32_t BS_BIN_MAX = 128;   // fuller bins are cut again rather than ranked by comparing,
+constexpr uint32_t BS_BIN_CUT = 32;    // and then these as well: cutting costs a block about 2 us, ranking 300 K
+                                       // values of 33 kinds in bins of up to 128 15 us (and of up to 64 6 us)
+constexpr uint32_t BS_REFINE = 3;      // times, at most
 
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 #pragma unroll
@@ -324,10 +326,10 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
     return v;
 }
 
-// Exclusive scan of h[0..n) in place by the whole block (n a multiple of NT
-// at most E NT); returns the largest element.
+// Exclusive scan of h[0..n), n at most E NT, in place by the whole block;
+// returns whether an element is above BS_BIN_MAX.
 template <uint32_t NT, uint32_t E>
-__device__ __forceinline__ uint32_t bs_scan(uint32_t *h, uint32_t n, uint32_t *scratch) {
+__device__ __forceinline__ bool bs_scan(uint32_t *h, uint32_t n, uint32_t *scratch) {
     uint32_t v[E], sum = 0, most = 0;
     const uint32_t per = (n + NT - 1) / NT, b = threadIdx.x * per;  // consecutive elements per thread
 #pragma unroll
@@ -344,14 +346,7 @@ __device__ __forceinline__ uint32_t bs_scan(uint32_t *h, uint32_t n, uint32_t *s
             h[b + u] = at;
             at += v[u];
         }
-#pragma unroll
-    for (uint32_t o = 32; o > 0; o >>= 1) most = max(most, (uint32_t)__shfl_xor(most, o, 64));
-    if ((threadIdx.x & 63u) == 0) scratch[threadIdx.x >> 6] = most;
-    __syncthreads();
-    most = 0;
-    for (uint32_t q = 0; q < NT / 64; ++q) most = max(most, scratch[q]);
-    __syncthreads();
-    return most;
+    return __syncthreads_or(most > BS_BIN_MAX) != 0;
 }
 
 __device__ __forceinline__ void bs_range(uint64_t &lo, uint64_t &hi, uint64_t *lohi, uint32_t nw) {
@@ -376,14 +371,15 @@ __device__ __forceinline__ uint32_t bs_bin(uint64_t x, uint64_t lo, double scale
 }
 
 // Puts the pairs x[u] (element u NT + thread of n) into order within their
-// bins: at[u] is bin << 16 | place in it, h the bins' first pairs and the end.
-// A pair's rank in a bin of up to BS_BIN_MAX is found by comparing; a fuller
+// bins, from out[base] on: at[u] is bin << 16 | place in it, h the bins' first
+// pairs and the end.  A pair's rank in a bin of up to `limit` is found by comparing; a fuller
 // bin's pairs are left as they come and the bin goes to the list heavy[1 ..],
 // counted in heavy[0].  (Sorting a bin by insertion, a thread per bin, took
 // stages_4m's launch, whose values repeat a few times each, from 42 to 98 us.)
 template <uint32_t NT, uint32_t E>
 __device__ __forceinline__ void bs_place(const uint64_t (&x)[E], uint32_t (&at)[E], uint32_t n, uint64_t *out,
-                                         const uint32_t *h, uint32_t *heavy) {
+                                         uint32_t base, const uint32_t *h, uint32_t limit, uint32_t *heavy) {
+    out += base;
 #pragma unroll
     for (uint32_t u = 0; u < E; ++u)
         if (u * NT + threadIdx.x < n) out[h[at[u] >> 16] + (at[u] & 0xffffu)] = x[u];
@@ -392,12 +388,12 @@ __device__ __forceinline__ void bs_place(const uint64_t (&x)[E], uint32_t (&at)[
     for (uint32_t u = 0; u < E; ++u) {
         if (u * NT + threadIdx.x < n) {
             const uint32_t s = h[at[u] >> 16], e = h[(at[u] >> 16) + 1], pl = at[u] & 0xffffu;
-            if (e - s <= BS_BIN_MAX) {
+            if (e - s <= limit) {
                 at[u] = s;
                 for (uint32_t q = s; q < e; ++q) at[u] += out[q] < x[u] ? 1u : 0u;
             } else {
                 at[u] = s + pl;
-                if (pl == 0) heavy[1 + atomicAdd(&heavy[0], 1u)] = s | (e - s) << 16;
+                if (pl == 0) heavy[1 + atomicAdd(&heavy[0], 1u)] = (base + s) | (e - s) << 16;
             }
         }
     }
@@ -408,55 +404,21 @@ __device__ __forceinline__ void bs_place(const uint64_t (&x)[E], uint32_t (&at)[
     __syncthreads();
 }
 
-// The pairs out[0..n) in order in place, n at most E NT, by the whole block;
-// h: BS_L1 + 1 words, spare: E NT / BS_BIN_MAX + 1.  For a bin that bs_sort_lds found too full: bins over
-// the bin's own range (values that repeat differ in their numbers, which are
-// evenly spread), and where that leaves one too full, a bitonic network whose
-// comparisons all ascend (a merge's first step pairs mirror images), so that
-// pairs past n need not exist.
-template <uint32_t NT, uint32_t E>
-__device__ void bs_sort_bin(uint64_t *out, uint32_t n, uint32_t *h, uint32_t *spare, uint32_t *scratch,
-                            uint64_t *lohi) {
-    const uint32_t nb = min(n, BS_L1);
-    uint64_t x[E], lo = ~0ull, hi = ~0ull;  // hi: of the complements
-#pragma unroll
-    for (uint32_t u = 0; u < E; ++u) {
-        const uint32_t i = u * NT + threadIdx.x;
-        x[u] = i < n ? out[i] : 0ull;
-        if (i < n) {
-            lo = x[u] < lo ? x[u] : lo;
-            hi = ~x[u] < hi ? ~x[u] : hi;
-        }
-    }
-    for (uint32_t i = threadIdx.x; i < nb; i += NT) h[i] = 0;
-    if (threadIdx.x == 0) spare[0] = 0;
-    bs_range(lo, hi, lohi, NT / 64);
-    const double scale = (double)nb / ((double)(hi - lo) + 1.0);
-    uint32_t at[E];
-#pragma unroll
-    for (uint32_t u = 0; u < E; ++u) {
-        at[u] = 0;
-        if (u * NT + threadIdx.x < n) {
-            const uint32_t bin = bs_bin(x[u], lo, scale, nb);
-            at[u] = bin << 16 | atomicAdd(&h[bin], 1u);
-        }
-    }
-    __syncthreads();
-    const uint32_t most = bs_scan<NT, (BS_L1 + NT - 1) / NT>(h, nb, scratch);
-    if (threadIdx.x == 0) h[nb] = n;
-    __syncthreads();
-    bs_place<NT, E>(x, at, n, out, h, spare);
-    if (most <= BS_BIN_MAX) return;
-    for (uint32_t k = 2; k < 2 * n; k <<= 1) {
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint32_t q = threadIdx.x; q < (n + 1) / 2 + j; q += NT) {
-                const uint32_t i = (q / j) * 2 * j + q % j;
-                const uint32_t l = j == k >> 1 ? i ^ (k - 1) : i + j;
+// Bitonic network over x[0..n) in place by the whole block; the comparisons
+// all ascend (bs_sort_lds).
+template <uint32_t NT>
+__device__ void bs_network(uint64_t *x, uint32_t n) {
+    for (uint64_t k = 2; k < 2ull * n; k <<= 1) {
+        uint64_t j = k >> 1;
+        for (int lj = __ffsll((unsigned long long)j) - 1; lj >= 0; --lj, j >>= 1) {
+            for (uint64_t q = threadIdx.x; q < (n + 1ull) / 2 + j; q += NT) {
+                const uint64_t i = (q >> lj) << (lj + 1) | (q & (j - 1));
+                const uint64_t l = j == k >> 1 ? i ^ (k - 1) : i + j;
                 if (l < n) {
-                    const uint64_t a = out[i], b = out[l];
+                    const uint64_t a = x[i], b = x[l];
                     if (b < a) {
-                        out[i] = b;
-                        out[l] = a;
+                        x[i] = b;
+                        x[l] = a;
                     }
                 }
             }
@@ -468,22 +430,104 @@ __device__ void bs_sort_bin(uint64_t *out, uint32_t n, uint32_t *h, uint32_t *sp
 // LDS of a block's sort.
 template <uint32_t NT, uint32_t CAP>
 struct BsLds {
+    // a listed bin holds more than BS_BIN_CUT of at most CAP pairs
+    static constexpr uint32_t HEAVY = CAP / (BS_BIN_CUT + 1);
     uint64_t out[CAP];
     uint64_t lohi[2 * NT / 64];
-    uint32_t h1[BS_L1 + 1], h2[CAP + 1];
-    // a listed bin holds more than BS_BIN_MAX of at most CAP pairs, also in
-    // the lists of bs_sort_bin, whose bin may be all of them
-    uint32_t heavy[CAP / BS_BIN_MAX + 1], spare[CAP / BS_BIN_MAX + 1];
+    union {
+        uint32_t h1[BS_L1 + 1];  // the first cut's bins
+        struct {                 // later: range of each listed bin's pairs
+            uint64_t lo[HEAVY];
+            union {
+                uint64_t hi[HEAVY];  // (of their complements)
+                double scale[HEAVY];
+            };
+        } r;
+    };
+    uint32_t h2[CAP + 1];
+    uint32_t heavy[2][HEAVY + 1];
     uint32_t scratch[NT / 64 + 1];
 };
+
+// The bins that `list` names (first pair | pairs << 16, the count in front),
+// each cut into as many as it has pairs over its own range, all of them at
+// once; those that stay too full go to `next`.
+template <uint32_t NT, uint32_t CAP>
+__device__ __forceinline__ void bs_refine(uint32_t n, const uint32_t *list, uint32_t *next, BsLds<NT, CAP> &l) {
+    constexpr uint32_t E = CAP / NT;
+    const uint32_t lane = threadIdx.x & 63u, nh = list[0];
+    // a single bin's pairs, or all
+    const uint32_t base = nh == 1 ? list[1] & 0xffffu : 0u;
+    if (nh == 1) n = list[1] >> 16;
+    for (uint32_t q = threadIdx.x; q < nh; q += NT) l.r.lo[q] = l.r.hi[q] = ~0ull;
+    for (uint32_t i = threadIdx.x; i < n; i += NT) l.h2[i] = 0;
+    if (threadIdx.x == 0) next[0] = 0;
+    __syncthreads();
+    uint64_t x[E];
+    uint32_t at[E];  // first the pair's listed bin, or ~0
+#pragma unroll
+    for (uint32_t u = 0; u < E; ++u) {
+        const uint32_t i = u * NT + threadIdx.x;
+        x[u] = i < n ? l.out[base + i] : 0ull;
+        at[u] = nh == 1 && i < n ? 0u : ~0u;
+    }
+    // a wave's 64 neighbours lie in few of them: each lane looks at one of the list
+    for (uint32_t q0 = 0; nh > 1 && q0 < nh; q0 += 64) {
+        const uint32_t v = q0 + lane < nh ? list[1 + q0 + lane] : 0u;  // (a listed bin is not empty)
+#pragma unroll
+        for (uint32_t u = 0; u < E; ++u) {
+            const uint32_t i = u * NT + threadIdx.x, i0 = i - lane;
+            uint64_t m = ballot((v & 0xffffu) < i0 + 64 && (v & 0xffffu) + (v >> 16) > i0);
+            for (; m; m &= m - 1) {
+                const uint32_t q = __ffsll((unsigned long long)m) - 1, w = __shfl(v, q, 64);
+                if (i - (w & 0xffffu) < w >> 16) at[u] = q0 + q;
+            }
+        }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < E; ++u)
+        if (at[u] != ~0u) {
+            // few pairs move a bin's ends: looking first saves the others the atomics
+            unsigned long long *lo = (unsigned long long *)&l.r.lo[at[u]], *hi = (unsigned long long *)&l.r.hi[at[u]];
+            if (x[u] < __hip_atomic_load(lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMin(lo, x[u]);
+            if (~x[u] < __hip_atomic_load(hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMin(hi, ~x[u]);
+        }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < nh; q += NT)
+        l.r.scale[q] = (double)(list[1 + q] >> 16) / ((double)(~l.r.hi[q] - l.r.lo[q]) + 1.0);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < E; ++u) {
+        const uint32_t i = u * NT + threadIdx.x;
+        if (at[u] != ~0u) {
+            const uint32_t s = (list[1 + at[u]] & 0xffffu) - base, c = list[1 + at[u]] >> 16;
+            const uint32_t bin = s + bs_bin(x[u], l.r.lo[at[u]], l.r.scale[at[u]], c);
+            at[u] = bin << 16 | atomicAdd(&l.h2[bin], 1u);
+        } else if (i < n) {  // in its place already
+            at[u] = i << 16;
+            l.h2[i] = 1;
+        }
+    }
+    __syncthreads();
+    const bool cut = bs_scan<NT, E>(l.h2, n, l.scratch);
+    if (threadIdx.x == 0) l.h2[n] = n;
+    __syncthreads();
+    bs_place<NT, E>(x, at, n, l.out, base, l.h2, cut ? BS_BIN_CUT : BS_BIN_MAX, next);
+}
 
 // Puts n <= CAP distinct pairs x[u] (element u NT + thread) into l.out in
 // ascending order.  They go to BS_L1 bins over their range, each cut into as
 // many as it has pairs, so that a smooth distribution, also over several
-// binades, puts about one into each; a bin's few pairs are ranked by
-// comparing, and bins too full for that are sorted one by one (a single level of n bins
-// took bucket_1m's launch 65 us instead of 16: its outer buckets span
-// binades).
+// binades, puts about one into each, and a bin's few pairs are ranked by
+// comparing (a single level of n bins took bucket_1m's launch 65 us instead of
+// 16: its outer buckets span binades).  Bins too full for that, the pairs of a
+// value that repeats (their numbers are evenly spread) or of narrow clusters,
+// are cut again over their own ranges; where BS_REFINE times leave one, a
+// bitonic network takes all pairs, whose comparisons all ascend (a merge's
+// first step pairs mirror images), so that pairs past n need not exist.
+// The full bins are cut together: one after the other by the whole block, 300 K
+// values of 33 kinds took the splitters' launch 114 us and the buckets' 33
+// (now 33 and 18), and the whole call 191 us (98; the radix sort 105).
 template <uint32_t NT, uint32_t CAP>
 __device__ __forceinline__ void bs_sort_lds(const uint64_t (&x)[CAP / NT], uint32_t n, BsLds<NT, CAP> &l) {
     constexpr uint32_t E = CAP / NT;
@@ -496,7 +540,7 @@ __device__ __forceinline__ void bs_sort_lds(const uint64_t (&x)[CAP / NT], uint3
         }
     for (uint32_t i = threadIdx.x; i < BS_L1; i += NT) l.h1[i] = 0;
     for (uint32_t i = threadIdx.x; i < n; i += NT) l.h2[i] = 0;
-    if (threadIdx.x == 0) l.heavy[0] = 0;
+    if (threadIdx.x == 0) l.heavy[0][0] = 0;
     bs_range(lo, hi, l.lohi, NT / 64);
     const double scale = (double)BS_L1 / ((double)(hi - lo) + 1.0);
 #pragma unroll
@@ -519,18 +563,22 @@ __device__ __forceinline__ void bs_sort_lds(const uint64_t (&x)[CAP / NT], uint3
         }
     }
     __syncthreads();
-    bs_scan<NT, E>(l.h2, n, l.scratch);
+    const bool cut = bs_scan<NT, E>(l.h2, n, l.scratch);
     if (threadIdx.x == 0) l.h2[n] = n;
     __syncthreads();
-    bs_place<NT, E>(x, at, n, l.out, l.h2, l.heavy);
-    const uint32_t nh = l.heavy[0];
-    for (uint32_t i = 0; i < nh; ++i)
-        bs_sort_bin<NT, E>(l.out + (l.heavy[1 + i] & 0xffffu), l.heavy[1 + i] >> 16, l.h1, l.spare, l.scratch, l.lohi);
+    bs_place<NT, E>(x, at, n, l.out, 0, l.h2, cut ? BS_BIN_CUT : BS_BIN_MAX, l.heavy[0]);
+    for (uint32_t r = 0; l.heavy[r & 1u][0] > 0; ++r) {
+        if (r == BS_REFINE) {
+            bs_network<NT>(l.out, n);
+            return;
+        }
+        bs_refine<NT, CAP>(n, l.heavy[r & 1u], l.heavy[(r + 1u) & 1u], l);
+    }
 }
 
 // Buckets of a tensor with nv values.
 __device__ __forceinline__ uint32_t bs_buckets(const TDesc &td, uint32_t nv) {
-    return nv <= BS_CAP ? 1u : min((nv + BS_AVG - 1) / BS_AVG, td.in.bsn);
+    return nv <= BS_CAP ? 1u : min((nv + BS_AVG - 1) / BS_AVG, (uint32_t)td.in.bsn);
 }
 
 __global__ __launch_bounds__(BS_SPLIT_THREADS) void k_bsort_split(Work w) {
@@ -609,30 +657,14 @@ __global__ __launch_bounds__(NTHREADS) void k_bsort_deal(Work w) {
 }
 
 // The whole tensor by one block, in global memory: for a bucket that outgrew
-// its room (improbable by the plan's bound and the sample's size).  The same
-// network as bs_sort_bin's, on the tensor's pairs.
+// its room (improbable by the plan's bound and the sample's size).
 __device__ void bs_sort_slow(const Work &w, const TDesc &td) {
     const uint32_t nv = td.nv;
     const uint64_t slot = td.in.slot;
     uint64_t *x = w.bspair + 2 * slot;
     for (uint32_t q = threadIdx.x; q < nv; q += BS_THREADS) x[q] = ((uint64_t)w.keyA[slot + q] << 32) | q;
     __syncthreads();
-    for (uint64_t k = 2; k < 2ull * nv; k <<= 1) {
-        for (uint64_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint64_t q = threadIdx.x; q < (nv + 1ull) / 2 + j; q += BS_THREADS) {
-                const uint64_t i = (q / j) * 2 * j + q % j;
-                const uint64_t l = j == k >> 1 ? i ^ (k - 1) : i + j;
-                if (l < nv) {
-                    const uint64_t a = x[i], b = x[l];
-                    if (b < a) {
-                        x[i] = b;
-                        x[l] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
+    bs_network<BS_THREADS>(x, nv);
     for (uint32_t r = threadIdx.x; r < nv; r += BS_THREADS) {
         const uint64_t v = x[r];
         w.vsorted[slot + r] = order_key_inv(~(uint32_t)(v >> 32));

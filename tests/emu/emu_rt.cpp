@@ -46,7 +46,18 @@ static Bar g_block;
 static Bar g_wave[16];
 static uint64_t g_xbuf[16][64];
 
+static std::atomic<int> g_or;
+
 void emu_block_barrier() { g_block.wait("block barrier"); }
+int emu_block_or(int v) {
+    if (v) g_or = 1;
+    g_block.wait("block or (write)");
+    const int r = g_or;
+    g_block.wait("block or (read)");
+    g_or = 0;
+    g_block.wait("block or (clear)");
+    return r;
+}
 uint64_t emu_wave_xchg(uint64_t v, uint32_t src) {
     const uint32_t w = threadIdx.x >> 6, l = threadIdx.x & 63u;
     g_xbuf[w][l] = v;

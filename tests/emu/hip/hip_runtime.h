@@ -1,5 +1,4 @@
-// Host emulation of the few HIP device facilities the bucketed-query kernels
-// use: every thread of a block is a std::thread, __syncthreads a block
+// Host emulation of the few HIP device facilities the emulated kernels use: every thread of a block is a std::thread, __syncthreads a block
 // barrier, wave intrinsics exchanges through a per-wave buffer.
 #pragma once
 #include <stdint.h>
@@ -27,10 +26,13 @@ extern dim3 blockDim, gridDim;
 #define __shared__ static
 #define __restrict__
 #define __HIP_MEMORY_SCOPE_AGENT 0
+#define __HIP_MEMORY_SCOPE_WORKGROUP 0
 void emu_block_barrier();
 uint64_t emu_wave_xchg(uint64_t v, uint32_t src_lane);  // every lane of the wave calls it
 inline uint32_t emu_lane() { return threadIdx.x & 63u; }
 inline void __syncthreads() { emu_block_barrier(); }
+int emu_block_or(int v);
+inline int __syncthreads_or(int v) { return emu_block_or(v); }
 #define __builtin_amdgcn_s_barrier() emu_block_barrier()
 #define __builtin_amdgcn_fence(...) std::atomic_thread_fence(std::memory_order_seq_cst)
 #define __builtin_amdgcn_wave_barrier() ((void)0)
@@ -78,6 +80,12 @@ inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f;
 inline int __clz(uint32_t x) { return x ? __builtin_clz(x) : 32; }
 inline uint32_t __umulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
 inline uint32_t atomicAdd(uint32_t *p, uint32_t v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
+inline unsigned long long atomicMin(unsigned long long *p, unsigned long long v) {
+    unsigned long long o = __atomic_load_n(p, __ATOMIC_SEQ_CST);
+    while (v < o && !__atomic_compare_exchange_n(p, &o, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST)) {
+    }
+    return o;
+}
 inline uint32_t atomicOr(uint32_t *p, uint32_t v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
 inline unsigned long long atomicAdd(unsigned long long *p, unsigned long long v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
 inline unsigned long long atomicOr(unsigned long long *p, unsigned long long v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
