@@ -430,7 +430,7 @@ void plan_bucket_sort(Plan &p, const std::vector<uint64_t> &most, bool own_pairs
     uint32_t at = 0;
     for (size_t t = 0; t < most.size(); ++t) {
         p.t[t].bs0 = at;
-        p.t[t].bsn = (uint16_t)n[t];
+        p.t[t].bsn = n[t];
         at += n[t];
     }
     p.carve.bs_total = total;
@@ -613,7 +613,7 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
         const bool even = cfg->segmentation == DR_SEG_EQUAL && cfg->n_seg >= 1;
         in.fit_run0 = (uint32_t)fit_runs;
         in.fit_blk0 = (uint32_t)fit_blocks;
-        in.fch = (uint16_t)fit_blocks_per_run(even ? ceil_div(most[t], runs_cap(most[t], degree, cfg->n_seg)) : most[t],
+        in.fch = fit_blocks_per_run(even ? ceil_div(most[t], runs_cap(most[t], degree, cfg->n_seg)) : most[t],
                                     cfg->fit_model);
         fit_runs += runs;
         fit_blocks += runs * in.fch;
@@ -1649,7 +1649,7 @@ dr_status dr_curvefit_encode(const float *vals, const uint64_t *n, uint64_t n_ca
     in.coef = coef_out;
     in.coef_stride = degree + 1;
     in.sigma = sigma_out;
-    in.fch = (uint16_t)fit_blocks_per_run(ceil_div(n_cap, runs_cap(n_cap, degree, n_seg)), DR_FIT_POLY);
+    in.fch = fit_blocks_per_run(ceil_div(n_cap, runs_cap(n_cap, degree, n_seg)), DR_FIT_POLY);
     p.carve.fit_blocks = (uint64_t)n_seg * in.fch;
     plan_bucket_sort(p, {n_cap}, true);
     p.carve.plan();

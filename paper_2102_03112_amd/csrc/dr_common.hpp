@@ -164,8 +164,8 @@ struct TInit {
     uint32_t rb0, rbn;   // blocks of the full histogram for a redo
     uint32_t fit_run0;   // first run of this tensor over all tensors
     uint32_t bs0;        // bucket sort: first bucket of this tensor
-    uint16_t bsn;        // bucket sort: buckets reserved (0: the radix sort)
-    uint16_t fch;        // partial-moment blocks per run
+    uint32_t bsn : 16,   // bucket sort: buckets reserved (0: the radix sort)
+        fch : 16;        // partial-moment blocks per run
 };
 
 // Chord segmentation over the whole grid (at most SEG_GRID_RUNS runs per
