@@ -716,11 +716,11 @@ __device__ __forceinline__ RecordView query_filter(const Work &w, const QueryOut
 // bandwidth for one bit each, and the chip serves about 266 G of them per
 // second; a random LDS read costs a CU a twelfth of that.  One 1024-thread
 // block runs per CU and keeps the first 137 KiB of the current tensor's
-// filter in LDS.  The hashes are tested in groups: an index is tested
-// against the LDS part with each hash of a group, and only if it passes is
-// one position of the group, the largest, read from memory (probe_group).
-// The group trades vector and LDS work for L2 reads (probe_hashes has the
-// rule): at share 0.31 of the filter in LDS, 0.8 reads per index instead of
+// filter in LDS.  Where it pays (probe_hashes has the rule), the hashes are
+// tested in groups: an index is tested against the LDS part with each hash of
+// a group, and only if it passes is one position of the group, the largest,
+// read from memory (probe_group).  The group trades vector and LDS work for L2
+// reads: at share 0.31 of the filter in LDS, 0.8 reads per index instead of
 // 1.4.  The pass is then bound by vector issue (about 110 instructions per
 // 64 indices), LDS reads (70% of their rate) and L2 reads (half of theirs)
 // alike.  gfx950 issues adds, right shifts and bit operations at twice the
@@ -738,9 +738,9 @@ __device__ __forceinline__ RecordView query_filter(const Work &w, const QueryOut
 // the next step's hashes are computed.  The code is kept small (one copy of
 // the emptying loop per kind of filter): with three copies a 37 k element
 // tensor's pass took 31 us instead of 19, in instruction fetches.
-// Against testing one hash at a time over the whole step (sender's,
-// receiver's pass in us): resnet50_25m 157, 179 -> 128, 146; vgg16_138m 479,
-// 536 -> 401, 480; transformer_355m_x24 1250-1510, 2000 -> 1003, 1408.
+// Against testing one hash at a time (probe_single; sender's, receiver's pass
+// in us): resnet50_25m 157, 179 -> 128, 146; vgg16_138m 479, 536 -> 401, 480;
+// transformer_355m_x24 1250-1510, 2000 -> 1003, 1408.
 constexpr uint32_t RUN_TILES = 512;  // most tiles per run (LDS tile counters)
 constexpr uint32_t RUN_TENSORS = 32;  // most tensors per run
 
@@ -889,28 +889,37 @@ __device__ void probe_scan(const Work &w, const QueryOut &o, uint32_t t_begin, u
     }
 }
 
-// Hashes per group, 1 to 4 and at most k.  More hashes per group trade
-// memory reads for vector work and LDS reads, so the smaller LDS's share of
-// the filter, the more pay off (sender's pass in us, standard layout):
-//   share 0.31 (25.6 M elements):    1: 161  2: 144  3: 132  4: 127
-//   share 0.54 (355 M, 24 tensors):  1: 1184 2: 1047 3: 994  4: 1105
-// An LDS share below a sixth rejects too little per hash to be worth testing
-// first (9 M elements, share 0.17: 76 us with four, 87 with one; 1 M
-// elements, 60% of them in the filter, share 0.13: 36 us with four, 33 with
-// one).  With the partitioned layout the first parts, those of the
-// first hashes, are the ones LDS holds: of three parts held (25.6 M
-// elements), groups of 2, 3 and 4 took 103, 110 and 115 us.  A filter that
-// LDS holds whole needs no memory read, and two hashes per group keep the
-// lanes of a step busy (1 M elements: 25.7 us with one, 22.8 with two).
-__device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout) {
-    uint32_t J;
-    if (lim >= m_bits)
-        J = 2u;
-    else if (layout == LAYOUT_PARTITIONED)
-        J = (uint64_t)lim * k >= 2ull * m_bits ? 2u : 1u;
-    else
-        J = 2ull * lim >= m_bits ? 3u : 6ull * lim >= m_bits ? 4u : 1u;
-    return min(J, max(k, 1u));
+// Hashes per group, 2 to 4 and at most k, or 0: one hash at a time.  A group
+// trades vector work and LDS reads, J hashes for every index and those of the
+// first two groups once more for the members, against memory reads, and works
+// on several steps at once.  So it pays where most indices are no members, LDS
+// holds a smaller share of the filter, and the block's share of the tiles (in
+// steps) is long enough for full windows.  Receiver's whole call in us, one hash at a time against the
+// group taken, by what decides:
+//   members, an eighth of the indices or more (estimated from the filter's
+//     size): 0.42 M elements, 60%: 62 and 68; 4 M, 25%: 106 and 110
+//   share of 0.6 and more, fewer than 512 steps: 8 M elements, 1%: 56
+//     and 66; 32 M: 132 and 136; 64 M equal; 256 M: 816 and 795
+//   share of 0.5, fewer than 96: 8 M: 66 and 69; 16 M: 98 and 95; 256 M: 970 and 815
+//   smaller shares: 0.31 (25.6 M): 176 and 145; 0.13 (60 M): 483 and 427;
+//     0.08 (100 M): 825 and 791.  There four hashes down to a share of a tenth
+//     and three below (0.06, 64 M: 585 and 576), and three at 0.5 and above.
+// With the partitioned layout the first parts, those of the first hashes, are
+// the ones LDS holds, and two are a group if it holds two parts and there are
+// 512 steps (25 M: 123 and 124; 60 M, two parts not held: 284 and 294; 24 x
+// 15 M: 1399 and 1258; 24 x 5 M: 441 and 410).  A filter that LDS holds whole needs no memory read, and two
+// hashes per group keep the lanes of a step busy, whatever the members (12 K
+// of 20 K elements: 54 and 49), but not for a tensor of a single step (three
+// of 100 elements: 24.8 and 26.8).
+__device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout, uint32_t d,
+                                                 uint32_t steps) {
+    const bool part = layout == LAYOUT_PARTITIONED;
+    if (lim >= m_bits && !part) return d > QWAVE ? min(2u, max(k, 1u)) : 0u;
+    // an m-bit filter of k hashes has about m ln 2 / k members
+    if (k < 2 || 11ull * m_bits >= 2ull * k * d) return 0u;
+    if (part) return steps < 512 || (uint64_t)lim * k < 2ull * m_bits ? 0u : 2u;
+    if (2ull * lim >= m_bits) return steps < (5ull * lim >= 3ull * m_bits ? 512u : 96u) ? 0u : min(3u, k);
+    return min(10ull * lim >= m_bits ? 4u : 3u, k);
 }
 
 // A tensor's filter as the probe pass's waves read it: the words of the bits
@@ -923,10 +932,9 @@ struct ProbeFilter {
     uint32_t m_bits, k, lim, J;
 };
 
-// How a filter is read: partly from LDS in groups of several hashes
-// (standard layout), partitioned, partly from LDS one hash at a time
-// (standard, LDS holds little of it), or all from LDS (standard).
-enum ProbeKind { PK_STANDARD = 0, PK_PARTITIONED = 1, PK_SINGLE = 2, PK_LDS = 3 };
+// How a filter is read: partly from LDS (standard layout), partitioned, or all
+// from LDS (standard).
+enum ProbeKind { PK_STANDARD = 0, PK_PARTITIONED = 1, PK_LDS = 2 };
 
 // Position of hash j (key rk): in the filter, or in its part j of k.
 template <int KIND>
@@ -1000,79 +1008,63 @@ __device__ __forceinline__ void queue_push(uint16_t *me, uint32_t &cnt, uint64_t
     cnt += popc64(mask);
 }
 
-// What groups 0 and 1 left of every hash, `step` (at most S) hashes of G
-// times 64 queue entries with their reads in flight together: of the first
-// two groups all but the position that was read there.  Groups of one: two
-// hashes at a time, and one while the queue is long, since an index that
-// fails the first costs the others' reads.  Returns the entries left, the
-// positives.
-template <int KIND, uint32_t G, uint32_t S>
+// Sets the queue's entries in mw, the window's bitmap.
+__device__ __forceinline__ void queue_mark(const uint16_t *me, uint32_t *mw, uint32_t cnt) {
+    for (uint32_t x = threadIdx.x & 63u; x < cnt; x += 64) {
+        const uint32_t e = me[x];
+        atomicOr(&mw[e >> 5], 1u << (e & 31u));
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// What groups 0 and 1 left of every hash, `step` (at most 4) hashes of 64 queue
+// entries with their reads in flight together: of the first two groups all but
+// the position that was read there.  Returns the entries left, the positives.
+template <int KIND>
 __device__ __forceinline__ uint32_t probe_rest(const ProbeFilter &f, uint16_t *me, uint32_t wbase, uint32_t cnt,
                                                uint32_t step) {
+    constexpr uint32_t S = 4;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t tested = min(2u * f.J, f.k);
     // where no bit of them is left, past them
-    uint32_t j0 = KIND == PK_LDS || KIND == PK_SINGLE || f.lim >= f.m_bits ? tested : 0u, n;
+    uint32_t j0 = KIND == PK_LDS || f.lim >= f.m_bits ? tested : 0u, n;
     for (; j0 < f.k && cnt > 0; j0 += n) {
         const uint32_t L = cnt;
-        n = min(S == 2 && L > 128 ? 1u : step, f.k - j0);
+        n = min(step, f.k - j0);
         cnt = 0;
-        for (uint32_t b0 = 0; b0 < L; b0 += 64 * G) {
-            uint32_t ev[G], acc[G], p[G][S], wd[G][S];
-            bool need[G][S];
+        for (uint32_t b0 = 0; b0 < L; b0 += 64) {
+            const uint32_t x = b0 + lane, ev = x < L ? me[x] : 0u, rk = mm3_rkey(wbase + ev);
+            uint32_t acc = x < L ? 1u : 0u, p[S], wd[S];
+            bool need[S];
 #pragma unroll
-            for (uint32_t g = 0; g < G; ++g) {
-                const uint32_t x = b0 + g * 64 + lane;
-                ev[g] = x < L ? me[x] : 0u;
-                acc[g] = x < L ? 1u : 0u;
-                if (g > 0 && b0 + g * 64 >= L) continue;
-                const uint32_t rk = mm3_rkey(wbase + ev[g]);
-#pragma unroll
-                for (uint32_t u = 0; u < S; ++u) {
-                    p[g][u] = 0u;
-                    if (u < n) {
-                        p[g][u] = probe_pos<KIND>(f, j0 + u, rk);
-                        if (j0 + u >= tested) acc[g] &= lds_bit<KIND>(f, p[g][u]);
-                    }
+            for (uint32_t u = 0; u < S; ++u) {
+                p[u] = 0u;
+                if (u < n) {
+                    p[u] = probe_pos<KIND>(f, j0 + u, rk);
+                    if (j0 + u >= tested) acc &= lds_bit<KIND>(f, p[u]);
                 }
             }
             if (KIND != PK_LDS) {
+                // the positions that groups 0 and 1 read
+                uint32_t done[S] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+                if (j0 < tested) {
+                    const uint32_t lo = max(p[0], p[1]), hi = max(p[2], p[3]);
+                    done[0] = done[1] = f.J >= 3 ? max(lo, hi) : lo;
+                    done[2] = done[3] = f.J >= 3 ? max(lo, hi) : hi;
+                }
 #pragma unroll
-                for (uint32_t g = 0; g < G; ++g) {
-                    if (g > 0 && b0 + g * 64 >= L) continue;
-                    // the positions that groups 0 and 1 read
-                    uint32_t done[S];
-#pragma unroll
-                    for (uint32_t u = 0; u < S; ++u) done[u] = 0xffffffffu;
-                    if (S == 4 && j0 < tested) {
-                        const uint32_t lo = max(p[g][0], p[g][1]), hi = max(p[g][S - 2], p[g][S - 1]);
-                        done[0] = done[1] = f.J >= 3 ? max(lo, hi) : lo;
-                        done[S - 2] = done[S - 1] = f.J >= 3 ? max(lo, hi) : hi;
-                        if (KIND == PK_PARTITIONED && f.J == 1) {
-                            done[0] = p[g][0];
-                            done[1] = p[g][1];
-                            done[S - 2] = done[S - 1] = 0xffffffffu;
-                        }
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < S; ++u) {
-                        need[g][u] = ((acc[g] & 1u) != 0u) & (u < n) & (p[g][u] >= f.lim) & (p[g][u] != done[u]);
-                        wd[g][u] = mem_word(f, p[g][u], need[g][u]);
-                    }
+                for (uint32_t u = 0; u < S; ++u) {
+                    need[u] = ((acc & 1u) != 0u) & (u < n) & (p[u] >= f.lim) & (p[u] != done[u]);
+                    wd[u] = mem_word(f, p[u], need[u]);
                 }
             }
             __builtin_amdgcn_wave_barrier();
+            uint64_t mask = ballot(acc & 1u);
+            if (KIND != PK_LDS) {
 #pragma unroll
-            for (uint32_t g = 0; g < G; ++g) {
-                if (g > 0 && b0 + g * 64 >= L) continue;
-                uint64_t mask = ballot(acc[g] & 1u);
-                if (KIND != PK_LDS) {
-#pragma unroll
-                    for (uint32_t u = 0; u < S; ++u)
-                        mask &= ballot(!need[g][u] | ((wd[g][u] >> (p[g][u] & 31u)) & 1u));
-                }
-                queue_push(me, cnt, mask, ev[g]);
+                for (uint32_t u = 0; u < S; ++u) mask &= ballot(!need[u] | ((wd[u] >> (p[u] & 31u)) & 1u));
             }
+            queue_push(me, cnt, mask, ev);
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -1108,15 +1100,8 @@ __device__ __forceinline__ void probe_drain(const ProbeFilter &f, uint16_t *me, 
         }
     }
     // what is left of every hash
-    if (KIND == PK_SINGLE)
-        cnt = probe_rest<KIND, 4, 2>(f, me, wbase, cnt, 2u);
-    else
-        cnt = probe_rest<KIND, 1, 4>(f, me, wbase, cnt, f.J == 3 ? 3u : 4u);
-    for (uint32_t x = lane; x < cnt; x += 64) {
-        const uint32_t e = me[x];
-        atomicOr(&mw[e >> 5], 1u << (e & 31u));
-    }
-    __builtin_amdgcn_wave_barrier();
+    cnt = probe_rest<KIND>(f, me, wbase, cnt, f.J == 3 ? 3u : 4u);
+    queue_mark(me, mw, cnt);
 }
 
 // The receiver's dense output starts as zeros, written while the filter reads
@@ -1192,6 +1177,84 @@ __device__ __forceinline__ void probe_window(const ProbeFilter &f, uint16_t *me,
     }
 }
 
+// Position p's word, its bit first: from LDS or from memory, from nowhere if not
+// `live`.
+__device__ __forceinline__ uint32_t probe_word(const ProbeFilter &f, uint32_t p, bool live) {
+    const bool in_lds = p < f.lim;
+    const uint32_t l = f.fc[in_lds ? p >> 5 : 0u];
+    const uint32_t g = mem_word(f, p, live & !in_lds);
+    return (in_lds ? l : g) >> (p & 31u);
+}
+
+// The same one hash at a time, over a step's 512 indices and then over those
+// that are left, four times 64 with their reads in flight together.  Once they
+// fit in 64 lanes (mostly positives, which take every hash) the round trips,
+// not the reads, are the cost: two hashes are then read together.
+template <int MODE, int KIND>
+__device__ __forceinline__ void probe_single(const ProbeFilter &f, uint16_t *me, uint32_t *mw, uint32_t wbase,
+                                             uint32_t nvalid, float *dz) {
+    constexpr uint32_t N = QWAVE / 64, G = 4;
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t s0 = 0; s0 < nvalid; s0 += QWAVE) {
+        if (MODE == Q_DECODE) zero_step(dz, s0, nvalid);
+        uint32_t wd[N], cnt = 0;
+#pragma unroll
+        for (uint32_t c = 0; c < N; ++c) {
+            const uint32_t e = s0 + c * 64 + lane;
+            bool need = e < nvalid;
+            // the sender's selection is known to be positive
+            if (MODE == Q_ENCODE) need = need & !((mw[e >> 5] >> (lane & 31u)) & 1u);
+            wd[c] = probe_word(f, probe_pos<KIND>(f, 0, mm3_rkey(wbase + e)), need);
+            wd[c] = need ? wd[c] : 0u;
+        }
+#pragma unroll
+        for (uint32_t c = 0; c < N; ++c) queue_push(me, cnt, ballot(wd[c] & 1u), s0 + c * 64 + lane);
+        for (uint32_t j = 1, n; j < f.k && cnt > 0; j += n) {
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t L = cnt;
+            cnt = 0;
+            n = 1;
+            if (L <= 64) {
+                n = min(f.k - j, 2u);
+                const bool act = lane < L;
+                const uint32_t e = act ? me[lane] : 0u, rk = mm3_rkey(wbase + e);
+                uint32_t all = act ? 1u : 0u;
+#pragma unroll
+                for (uint32_t u = 0; u < 2; ++u)
+                    if (u < n) all &= probe_word(f, probe_pos<KIND>(f, j + u, rk), act);
+                __builtin_amdgcn_wave_barrier();
+                queue_push(me, cnt, ballot(all & 1u), e);
+                continue;
+            }
+            for (uint32_t b0 = 0; b0 < L; b0 += 64 * G) {
+                uint32_t ev[G], bw[G];
+#pragma unroll
+                for (uint32_t u = 0; u < G; ++u) {
+                    const uint32_t x = b0 + u * 64 + lane;
+                    ev[u] = x < L ? me[x] : 0u;
+                    bw[u] = 0u;
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < G; ++u) {
+                    if (b0 + u * 64 >= L) break;  // this group and the ones after it are empty
+                    const bool live = b0 + u * 64 + lane < L;
+                    const uint32_t x = probe_word(f, probe_pos<KIND>(f, j, mm3_rkey(wbase + ev[u])), live);
+                    bw[u] = live ? x : 0u;
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (uint32_t u = 0; u < G; ++u) {
+                    if (b0 + u * 64 >= L) break;
+                    queue_push(me, cnt, ballot(bw[u] & 1u), ev[u]);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        queue_mark(me, mw, cnt);
+    }
+}
+
 // A wave's window: ns steps from step `st` of a tile of the tensor at tile0,
 // d elements from `off`.  Writes its words of the positives bitmap and, for
 // the receiver, its zeros; returns its positives.
@@ -1218,14 +1281,16 @@ __device__ __forceinline__ uint32_t probe_take(const Work &w, const QueryOut &o,
         for (uint32_t s0 = 0; s0 < nvalid; s0 += QWAVE) zero_step(dz, s0, nvalid);
     if (!pre) {
         if (f.k > 0 && nvalid > 0) {
-            if (part)
-                probe_window<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
-            else if (all_lds)
+            if (all_lds && !part && J != 0)
                 probe_window<MODE, PK_LDS>(f, me, mw, wbase, nvalid, dz);
-            else if (J == 1)
-                probe_window<MODE, PK_SINGLE>(f, me, mw, wbase, nvalid, dz);
-            else
+            else if (J != 0 && !part)
                 probe_window<MODE, PK_STANDARD>(f, me, mw, wbase, nvalid, dz);
+            else if (J != 0)
+                probe_window<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
+            else if (part)
+                probe_single<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
+            else
+                probe_single<MODE, PK_STANDARD>(f, me, mw, wbase, nvalid, dz);
         }
         word = mw[lane];
         if (lane < nwords) w.pbits[word0 + lane] = word;
@@ -1295,7 +1360,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
         const uint32_t d = td.in.d, tile0 = td.in.tile0, k = uni(rv.k);
         const bool part = uni(rv.layout) == LAYOUT_PARTITIONED;
         const uint32_t lim = uni(fcw * 32u);
-        const uint32_t J = uni(probe_hashes(rv.m_bits, k, lim, rv.layout));
+        const uint32_t J = uni(probe_hashes(rv.m_bits, k, lim, rv.layout, d, (t_end - t_begin) * QPT));
         const ProbeFilter f{fc, ps, buffer_view(rv.bits, rv.m_bits / 8u), uni(rv.m_bits), k, lim, J};
         uint16_t *me = qe[wv];
         uint32_t *mw = lw[wv];
@@ -1420,7 +1485,9 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe_many(Work w, QueryOut o) {
         __syncthreads();
         const uint32_t m0 = uni(v_m), lim0 = uni(v_words) * 32u;
         const __amdgpu_buffer_rsrc_t bits0 = buffer_view((const void *)(uintptr_t)uni(v_bits), m0 / 8u);
-        const uint32_t J0 = uni(probe_hashes(m0, uni(v_k), lim0, part ? LAYOUT_PARTITIONED : LAYOUT_STANDARD));
+        const uint32_t J0 = all_lds ? 2u  // (at most each tensor's k)
+                                    : uni(probe_hashes(m0, uni(v_k), lim0, part ? LAYOUT_PARTITIONED : LAYOUT_STANDARD,
+                                                       uni(v_d), (t_end - t_begin) * QPT));
         uint16_t *me = qe[wv];
         uint32_t *mw = lw[wv];
         const Windows win(nq);
@@ -1434,7 +1501,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe_many(Work w, QueryOut o) {
             const uint32_t sl = popc64(ballot(lane < nrun && v_tile0 <= tile)) - 1;  // the tile's tensor
             const uint32_t k = __builtin_amdgcn_readlane(v_k, sl);
             const ProbeFilter f{fc + __builtin_amdgcn_readlane(v_base, sl), ps, bits0,
-                                (uint32_t)__builtin_amdgcn_readlane(v_m, sl), k, lim0, all_lds ? min(2u, max(k, 1u)) : J0};
+                                (uint32_t)__builtin_amdgcn_readlane(v_m, sl), k, lim0, min(J0, max(k, 1u))};
             const uint64_t off = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(v_off[1], sl) << 32) |
                                  (uint32_t)__builtin_amdgcn_readlane(v_off[0], sl);
             const uint32_t total =

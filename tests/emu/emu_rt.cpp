@@ -67,6 +67,17 @@ uint64_t emu_wave_xchg(uint64_t v, uint32_t src) {
     return r;
 }
 
+uint64_t emu_wave_ballot(bool p) {
+    const uint32_t w = threadIdx.x >> 6, l = threadIdx.x & 63u;
+    g_xbuf[w][l] = p ? 1u : 0u;
+    g_wave[w].wait("wave ballot (write)");
+    uint64_t m = 0;
+    for (uint32_t s = 0; s < std::min<uint32_t>(64, blockDim.x - 64 * w); ++s) m |= g_xbuf[w][s] << s;
+    g_wave[w].wait("wave ballot (read)");
+    return m;
+}
+void emu_wave_barrier() { g_wave[threadIdx.x >> 6].wait("wave barrier"); }
+
 void emu_launch(uint32_t grid, uint32_t nt, const std::function<void()> &body) {
     gridDim.x = grid;
     blockDim.x = nt;

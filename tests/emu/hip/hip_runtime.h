@@ -35,7 +35,13 @@ int emu_block_or(int v);
 inline int __syncthreads_or(int v) { return emu_block_or(v); }
 #define __builtin_amdgcn_s_barrier() emu_block_barrier()
 #define __builtin_amdgcn_fence(...) std::atomic_thread_fence(std::memory_order_seq_cst)
+#ifdef EMU_WAVE_IN_STEP  // kernels whose lanes pass data through LDS with no block barrier
+void emu_wave_barrier();
+#define __builtin_amdgcn_wave_barrier() emu_wave_barrier()
+#else
 #define __builtin_amdgcn_wave_barrier() ((void)0)
+#endif
+#define __builtin_amdgcn_inverse_ballot_w64(m) ((((uint64_t)(m)) >> emu_lane()) & 1u)
 #define __builtin_amdgcn_s_sleep(n) std::this_thread::yield()
 #define __builtin_amdgcn_readfirstlane(x) (x)
 inline uint32_t __builtin_amdgcn_mbcnt_lo(uint32_t m, uint32_t x) {
@@ -46,11 +52,8 @@ inline uint32_t __builtin_amdgcn_mbcnt_hi(uint32_t m, uint32_t x) {
     const uint32_t l = emu_lane();
     return x + (l < 32 ? 0u : (uint32_t)__builtin_popcount(m & ((1u << (l - 32)) - 1u)));
 }
-inline uint64_t __ballot(bool p) {
-    uint64_t m = 0;
-    for (uint32_t s = 0; s < 64; ++s) m |= (emu_wave_xchg(p ? 1u : 0u, s) & 1ull) << s;
-    return m;
-}
+uint64_t emu_wave_ballot(bool p);  // every lane of the wave calls it
+inline uint64_t __ballot(bool p) { return emu_wave_ballot(p); }
 template <typename T>
 inline T emu_shfl(T v, uint32_t src) {
     uint64_t raw = 0;

@@ -1,7 +1,7 @@
-"""The full-range query over the forms its hash groups take: filters that the
-LDS copy holds whole, to the last word, or in part, one to thirteen hashes,
-ragged windows, and filters so full that the survivor queues overflow.  Bit-exact
-against the oracle's query."""
+"""The full-range query over the forms its hash groups take, and one hash at a
+time: filters that the LDS copy holds whole, to the last word, or in part, one to
+thirteen hashes, ragged windows, and filters so full that the survivor queues
+overflow.  Bit-exact against the oracle's query."""
 import numpy as np
 import pytest
 
@@ -21,6 +21,9 @@ FILTERS = [
     (LDS_BITS * 3, 5, 0.97, 50_000), (LDS_BITS * 6, 13, 0.6, 33_000), (LDS_BITS * 6 + 32, 13, 0.6, 33_000),
     (LDS_BITS * 9, 2, 0.98, 12_289), (LDS_BITS * 2, 13, 1.0, 8193), (LDS_BITS * 9, 13, 1.0, 8193),
     (LDS_BITS, 13, 1.0, 8193),
+    # few members, so that groups of four, of three and (96 steps a block) of three again read memory
+    (LDS_BITS * 3, 10, 0.5, 2_000_003), (LDS_BITS * 4 + 32, 13, 0.55, 2_200_001), (LDS_BITS * 12, 13, 0.5, 6_000_001),
+    (LDS_BITS * 2 - 32, 10, 0.5, 12_700_001),
 ]
 
 
@@ -70,3 +73,37 @@ def test_round_trip_of_many_tensors(tensors, spread, layout):
     cfg = B.Config(off, (1, 4), 1e-3, 3, 2, filter_layout=layout)
     refs = oracle.roundtrip(g, off, (1, 4), 1e-3, 3, 2, layout=layout)
     check_roundtrip(g, cfg, run_roundtrip(g, cfg), refs)
+
+
+@pytest.mark.parametrize("tensors,d,layout", [(14, 4_800_003, 0), (14, 4_800_003, 1), (6, 12_000_001, 0),
+                                              (6, 12_000_001, 1), (3, 23_000_001, 0)])
+def test_groups_and_single_hashes_agree(tensors, d, layout):
+    """A batch long enough for groups of hashes against its tensors one by one,
+    which are tested one hash at a time or, the largest, in other groups: the same
+    records, dense values and positives."""
+    import torch
+
+    log(f"{tensors} x {d} layout={layout}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + layout)
+    off = [d * t for t in range(tensors + 1)]
+    g = torch.randn(off[-1], generator=gen, device="cuda") * 1e-3
+    cfg, one = B.Config(off, (1, 100), 1e-3, 3, 4, filter_layout=layout), B.Config([0, d], (1, 100), 1e-3, 3, 4,
+                                                                                filter_layout=layout)
+
+    def trip(x, c):
+        total, rec = B.payload_layout(c)
+        pay = torch.zeros(total, dtype=torch.uint8, device="cuda")
+        dense = torch.full((c.d,), 9.0, device="cuda")
+        counts = torch.zeros(4 * c.n_tensors, dtype=torch.int64, device="cuda")
+        B.roundtrip(x, c, pay, dense, None, None, counts, workspace(c.d, c.n_tensors))
+        sync()
+        return pay, rec, dense, counts
+
+    pay, rec, dense, counts = trip(g, cfg)
+    for t in range(tensors):
+        p1, _, d1, c1 = trip(g[off[t]:off[t + 1]], one)
+        n = B.parse_record(host(p1), 0).rec_bytes
+        assert torch.equal(counts[4 * t:4 * t + 4], c1) and int(c1[3]) == 0
+        assert torch.equal(pay[rec[t]:rec[t] + n], p1[:n])
+        assert torch.equal(dense[off[t]:off[t + 1]], d1)
