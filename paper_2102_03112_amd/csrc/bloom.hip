@@ -2237,6 +2237,10 @@ static void launch_probe(const Work &w, const QueryOut &o, int grid, hipStream_t
         k_probe_many<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
     else
         k_probe<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
+    static const char *const names[2][4] = {
+        {"k_probe<Q_ENCODE>", "k_probe<Q_PLAIN>", "k_probe<Q_DECODE>", "k_probe<Q_SUM>"},
+        {"k_probe_many<Q_ENCODE>", "k_probe_many<Q_PLAIN>", "k_probe_many<Q_DECODE>", "k_probe_many<Q_SUM>"}};
+    trace_mark(s, names[w.tiny > 0 ? 1 : 0][MODE]);
 }
 
 hipError_t launch_query_encode(const Work &w, const float *g, int grid_persist, uint64_t *counts_out, hipStream_t s,
@@ -2248,7 +2252,6 @@ hipError_t launch_query_encode(const Work &w, const float *g, int grid_persist, 
     // the pass also scans its tile counts (probe_scan) and writes the
     // records' headers
     launch_probe<Q_ENCODE>(w, o, probe_grid(w), s);
-    trace_mark(s, "k_probe<Q_ENCODE>");
     if (after_probe) {
         hipError_t e = hipEventRecord(after_probe, s);
         if (e != hipSuccess) return e;
@@ -2288,7 +2291,6 @@ hipError_t launch_query_plain(const Work &w, uint32_t *idx_out, uint64_t cap, ui
     o.n_out = n_out;
     // the pass also scans its tile counts (probe_scan)
     launch_probe<Q_PLAIN>(w, o, probe_grid(w), s);
-    trace_mark(s, "k_probe<Q_PLAIN>");
     k_emit<Q_PLAIN><<<resident_grid(k_emit<Q_PLAIN>, EMIT_THREADS, w.ntiles_total), EMIT_THREADS, 0, s>>>(w, o);
     trace_mark(s, "k_emit<Q_PLAIN>");
     return hipGetLastError();
@@ -2303,7 +2305,6 @@ hipError_t launch_probe_decode(const Work &w, float *dense_out, uint64_t *counts
     const uint32_t grid = std::min<uint32_t>((uint32_t)probe_grid(w), std::max<uint32_t>(1u, max_blocks));
     // the pass also scans its tile counts (probe_scan)
     launch_probe<Q_DECODE>(w, o, (int)grid, s);
-    trace_mark(s, "k_probe<Q_DECODE>");
     return hipGetLastError();
 }
 
@@ -2334,7 +2335,6 @@ hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens,
     o.ntiles1 = ntiles1;
     // the pass also scans its tile counts (probe_scan)
     launch_probe<Q_SUM>(w, o, probe_grid(w), s);
-    trace_mark(s, "k_probe<Q_SUM>");
     k_emit_sum<<<resident_grid(k_emit_sum, SUM_THREADS, ntiles1), SUM_THREADS, 0, s>>>(w, o);
     trace_mark(s, "k_emit_sum");
     return hipGetLastError();

@@ -719,15 +719,15 @@ __global__ __launch_bounds__(BS_THREADS) void k_bsort_bucket(Work w) {
 
 hipError_t launch_sort(const Work &w, uint32_t cap_tiles, hipStream_t s) {
     const uint32_t cus = (uint32_t)device_cus();
-    if (w.bstotal) {  // (timed under the names of the radix sort's launches)
+    if (w.bstotal) {
         if (w.bsmulti) {
             k_bsort_split<<<w.ntensors, BS_SPLIT_THREADS, 0, s>>>(w);
-            trace_mark(s, "k_sort_upfront");
+            trace_mark(s, "k_bsort_split");
             k_bsort_deal<<<std::max(1u, std::min(cap_tiles, cus * 4u)), NTHREADS, 0, s>>>(w);
-            trace_mark(s, "k_sort_pass");
+            trace_mark(s, "k_bsort_deal");
         }
         k_bsort_bucket<<<w.bstotal, BS_THREADS, 0, s>>>(w);
-        trace_mark(s, "k_sort_pass");
+        trace_mark(s, "k_bsort_bucket");
         return hipGetLastError();
     }
     k_sort_upfront<<<cus, NTHREADS, 0, s>>>(w, w.keyA);

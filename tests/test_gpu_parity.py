@@ -668,7 +668,7 @@ def test_trace_attributes_both_streams():
     B.trace_begin()
     run_roundtrip(g, cfg)
     tr = B.trace_end()
-    for k in ("k_probe<Q_ENCODE>", "k_probe<Q_DECODE>", "k_sort_pass", "k_emit<Q_DECODE>"):
+    for k in ("k_probe<Q_ENCODE>", "k_probe<Q_DECODE>", "k_bsort_bucket", "k_emit<Q_DECODE>"):
         assert k in tr and tr[k][0] >= 1 and tr[k][1] > 0, k
 
 
