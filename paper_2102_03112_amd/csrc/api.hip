@@ -705,11 +705,28 @@ void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t
     }
 }
 
-// Tensors of fewer tiles than a 256th of all, a probe block's share.
-uint32_t tiny_tensors(const std::vector<TInit> &t, uint64_t ntiles) {
-    uint32_t n = 0;
-    for (const TInit &in : t) n += in.ntiles < ceil_div(ntiles, 256) ? 1u : 0u;
-    return n;
+// Whether the probe pass's runs take several tensors (k_probe_many).  A block
+// runs over each tensor that its share of the tiles holds; a run costs it its
+// set-up and barriers, about what 7 steps of 512 indices take, and looking
+// tensors up costs every step about 1/26 of itself.  So runs are shared where
+// the block that is last to finish would have enough of them (receiver's call
+// in us, a run each against shared ones): 240 x (100 K, 1 K) elements, 5 runs
+// in 192 steps: 139 and 125; 300 x 40 K, 2 in 96: 79 and 73; 8 x (3 M, 1 K), 3
+// in 192: 102 and 100; 24 x (3 M, 1 K), 3 in 552: 211 and 212; 8 x (15 M, 1 M,
+// 1 K, 1 K), 4 in 984: 463 and 475; 12 M, 12 M and 100, 2 in 184: 136 and 145.
+bool shared_runs(const std::vector<TInit> &t, uint64_t ntiles) {
+    constexpr uint64_t RUN = 7, STEPS = TILE / 512;
+    const uint64_t per = std::max<uint64_t>(1, ceil_div(ntiles, 256)), steps = per * STEPS;
+    uint64_t most = 0, runs = 1, block = 0;
+    for (const TInit &in : t) {
+        if (in.tile0 / per != block) {
+            block = in.tile0 / per;
+            runs = 1;
+        }
+        if (in.tile0 % per != 0) ++runs;  // the share's first tile begins a run whatever starts there
+        most = std::max(most, std::min(per, ntiles - block * per) * STEPS + RUN * runs);
+    }
+    return most > steps + RUN && (most - steps - RUN) * 26 > steps;
 }
 
 // Descriptors and the zeroed regions; a query-only work has no histogram or
@@ -807,7 +824,7 @@ dr_status encode_prepare(const float *g, const dr_config *cfg, uint8_t *payload,
     }
     e.w = e.p.carve.view((uint8_t *)ws);
     e.w.counts_out = counts_out;
-    e.w.tiny = tiny_tensors(e.p.t, e.p.carve.ntiles);
+    e.w.shared = shared_runs(e.p.t, e.p.carve.ntiles);
     return DR_OK;
 }
 
@@ -879,7 +896,7 @@ dr_status decode_prepare(const uint8_t *payload, const dr_config *cfg, float *de
         dd.p.t[t] = receiver_init(dd.p.t[t]);
     }
     dd.w = dd.p.carve.view((uint8_t *)ws);
-    dd.w.tiny = tiny_tensors(dd.p.t, dd.p.carve.ntiles);
+    dd.w.shared = shared_runs(dd.p.t, dd.p.carve.ntiles);
     dd.dense_out = dense_out;
     dd.idx_out = idx_out;
     dd.val_out = val_out;
@@ -1000,7 +1017,7 @@ dr_status roundtrip_impl(const float *g, const dr_config *cfg, uint8_t *payload,
         // stream runs it (once the caller's earlier work on s is done) while
         // the sender selects
         dd.w = qc.view((uint8_t *)ws + qoff);
-        dd.w.tiny = e.w.tiny;
+        dd.w.shared = e.w.shared;
         dd.w.qlist = e.w.qlist;
         dd.w.qbkt = e.w.qbkt;
         dd.w.qtab = e.w.qtab;
@@ -1148,7 +1165,7 @@ dr_status decode_sum_impl(const uint8_t *const *payloads, uint32_t npay, const d
     if (!ws_ok(ws, ws_bytes, c.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", c.bytes);
     Work w = c.view((uint8_t *)ws);
-    w.tiny = tiny_tensors(vt, c.ntiles);
+    w.shared = shared_runs(vt, c.ntiles);
     trace_call(s);
     DR_HIP(run_init(w, vt, s, true, {counts_out, counts_out ? 8 * T * npay : 0}));
     DR_HIP(launch_query_decode_sum(w, npay, (uint32_t)T, (uint32_t)ntiles1, scale, dense_out, counts_out, s));

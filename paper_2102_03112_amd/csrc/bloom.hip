@@ -1392,7 +1392,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
 
 // The same with runs of as many whole tensors as the LDS copy has room for,
 // so that a model's small layers share a run's set-up and barriers
-// (launch_probe).  A run's tensors are held one per lane.
+// (where the host's plan finds that it pays).  A run's tensors are held one per lane.
 template <int MODE>
 __global__ __launch_bounds__(PB_THREADS) void k_probe_many(Work w, QueryOut o) {
     __shared__ uint32_t fc[FC_WORDS + 1];
@@ -2225,22 +2225,16 @@ static int probe_grid(const Work &w) {
     return (int)std::max(1u, std::min(cus, by_tiles));
 }
 
-// Runs of several tensors where some are smaller than a block's share of the
-// tiles (a model's biases and small layers): a run each would make the block
-// that holds the most of them the last to finish (161 layers of 25.6 M
-// elements: receiver's pass 113 us with a run each, 80 with shared ones).
-// The lookups cost the pass of a few large tensors 3%, so these keep a run
-// each (24 tensors, 355 M elements: 1408 against 1458 us).
 template <int MODE>
 static void launch_probe(const Work &w, const QueryOut &o, int grid, hipStream_t s) {
-    if (w.tiny > 0)
+    if (w.shared)
         k_probe_many<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
     else
         k_probe<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
     static const char *const names[2][4] = {
         {"k_probe<Q_ENCODE>", "k_probe<Q_PLAIN>", "k_probe<Q_DECODE>", "k_probe<Q_SUM>"},
-        {"k_probe_many<Q_ENCODE>", "k_probe_many<Q_PLAIN>", "k_probe_many<Q_DECODE>", "k_probe_many<Q_SUM>"}};
-    trace_mark(s, names[w.tiny > 0 ? 1 : 0][MODE]);
+        {"k_probe_many<Q_ENCODE>", "", "k_probe_many<Q_DECODE>", "k_probe_many<Q_SUM>"}};
+    trace_mark(s, names[w.shared ? 1 : 0][MODE]);
 }
 
 hipError_t launch_query_encode(const Work &w, const float *g, int grid_persist, uint64_t *counts_out, hipStream_t s,
@@ -2290,7 +2284,8 @@ hipError_t launch_query_plain(const Work &w, uint32_t *idx_out, uint64_t cap, ui
     o.cap = cap;
     o.n_out = n_out;
     // the pass also scans its tile counts (probe_scan)
-    launch_probe<Q_PLAIN>(w, o, probe_grid(w), s);
+    k_probe<Q_PLAIN><<<probe_grid(w), PB_THREADS, 0, s>>>(w, o);  // (one tensor)
+    trace_mark(s, "k_probe<Q_PLAIN>");
     k_emit<Q_PLAIN><<<resident_grid(k_emit<Q_PLAIN>, EMIT_THREADS, w.ntiles_total), EMIT_THREADS, 0, s>>>(w, o);
     trace_mark(s, "k_emit<Q_PLAIN>");
     return hipGetLastError();

@@ -254,7 +254,7 @@ struct Work {
     uint32_t *tile_tensor;    // tensor of each tile (filled by k_init)
     uint32_t ntensors;
     uint32_t ntiles_total;    // sum of ntiles
-    uint32_t tiny;            // tensors of fewer tiles than a probe block's share
+    bool shared;              // the probe pass's runs take several tensors
     uint64_t slots;           // padded elements = ntiles_total * TILE
     uint64_t *pstat;          // probe pass look-back: per block (flag << 62 | trailing count), zeroed at set-up
     uint32_t *tcnt;           // per-tile counts of the current ordered pass

@@ -62,8 +62,8 @@ def test_round_trip_with_large_filters(d, ratio, fpr, layout):
 @pytest.mark.parametrize("layout", [0, 1], ids=["standard", "partitioned"])
 @pytest.mark.parametrize("tensors,spread", [(300, 4000), (67, 40_000), (40, 1)])
 def test_round_trip_of_many_tensors(tensors, spread, layout):
-    """Blocks whose runs hold many tensors at once, empty and one-element
-    tensors among them, and set-up over several launches."""
+    """Blocks whose share holds a few tensors, empty and one-element tensors
+    among them (40), and set-up over several launches."""
     rng = np.random.default_rng(tensors)
     sizes = rng.integers(0, spread + 1, tensors)
     sizes[tensors // 2] = 300_000  # a filter larger than what LDS keeps
@@ -73,6 +73,76 @@ def test_round_trip_of_many_tensors(tensors, spread, layout):
     cfg = B.Config(off, (1, 4), 1e-3, 3, 2, filter_layout=layout)
     refs = oracle.roundtrip(g, off, (1, 4), 1e-3, 3, 2, layout=layout)
     check_roundtrip(g, cfg, run_roundtrip(g, cfg), refs)
+
+
+@pytest.fixture(scope="module")
+def shared():
+    """Shares of 41 tiles over 9400 tensors, so that runs are shared and end at 32
+    tensors, at a full LDS copy (10 tensors of 8 to 20 K elements, 14.4 bits
+    each), at a filter larger than it and at the end of the share; empty and
+    one-element tensors among them."""
+    rng = np.random.default_rng(9)
+    sizes = rng.integers(0, 41, 9400)
+    mid = np.concatenate([np.arange(200, 500), rng.choice(np.arange(600, 9000), 100, replace=False)])
+    sizes[mid] = rng.integers(8000, 20_001, mid.size)
+    sizes[[100, 4700]] = 90_000
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    cfg = B.Config(off, (1, 2), 1e-6, 2, 2)
+    gs = [(np.random.default_rng(90 + p).standard_normal(cfg.d) * 1e-3).astype(np.float32) for p in range(2)]
+    refs = [oracle.roundtrip(g, off, (1, 2), 1e-6, 2, 2) for g in gs]
+    return cfg, gs, refs, np.sort(mid)
+
+
+def traced(call):
+    """The kernels that the call launched."""
+    B.trace_begin()
+    call()
+    sync()
+    return B.trace_end()
+
+
+def test_round_trip_of_shared_runs(shared):
+    cfg, gs, refs, _ = shared
+    log(f"{cfg.n_tensors} tensors, {cfg.d} elements")
+    outs = []
+    kernels = traced(lambda: outs.append(run_roundtrip(gs[0], cfg)))
+    assert {"k_probe_many<Q_ENCODE>", "k_probe_many<Q_DECODE>"} <= set(kernels)
+    check_roundtrip(gs[0], cfg, outs[0], refs[0])
+
+
+def test_damaged_records_among_shared_runs(shared):
+    """A record with a damaged header inside a run is flagged and left out, by
+    the receiver and by the summing receiver; the others are whole."""
+    import torch
+
+    cfg, gs, refs, mid = shared
+    T, off = cfg.n_tensors, cfg.offsets.astype(np.int64)
+    ws = workspace(cfg.d, T)
+    outs = [run_roundtrip(g, cfg) for g in gs]
+    pays = [o["payload"] for o in outs]
+    damaged = [int(mid[40]), 5000, 9399]
+    for t in damaged:
+        pays[1][outs[1]["rec_off"][t]] ^= 0xFF  # magic
+    pays = [dev_tensor(p) for p in pays]
+    dense = torch.full((cfg.d,), 9.0, device="cuda")
+    counts = torch.zeros(4 * T, dtype=torch.int64, device="cuda")
+    kernels = traced(lambda: B.payload_decode(pays[1], cfg, dense, None, None, counts, ws))
+    assert "k_probe_many<Q_DECODE>" in kernels
+    want = outs[1]["dense"].copy()
+    for t in damaged:
+        want[off[t]:off[t + 1]] = 0.0
+    np.testing.assert_array_equal(host(dense), want)
+    flags = host(counts).reshape(T, 4)[:, 3]
+    assert sorted(np.flatnonzero(flags)) == sorted(damaged) and all(flags[t] & B.FLAG_DEC_MISMATCH for t in damaged)
+
+    total = torch.full((cfg.d,), 9.0, device="cuda")
+    counts = torch.zeros(8 * T, dtype=torch.int64, device="cuda")
+    ws2 = B.workspace(2 * cfg.d, 2 * T)
+    kernels = traced(lambda: B.payload_decode_sum(pays, cfg, 0.5, total, counts, ws2))
+    assert "k_probe_many<Q_SUM>" in kernels
+    np.testing.assert_array_equal(host(total), np.float32(0.5) * (outs[0]["dense"] + want))
+    flags = host(counts).reshape(2, T, 4)[:, :, 3]
+    assert not flags[0].any() and sorted(np.flatnonzero(flags[1])) == sorted(damaged)
 
 
 @pytest.mark.parametrize("tensors,d,layout", [(14, 4_800_003, 0), (14, 4_800_003, 1), (6, 12_000_001, 0),
