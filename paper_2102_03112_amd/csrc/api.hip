@@ -1168,7 +1168,10 @@ dr_status decode_sum_impl(const uint8_t *const *payloads, uint32_t npay, const d
     w.shared = shared_runs(vt, c.ntiles);
     trace_call(s);
     DR_HIP(run_init(w, vt, s, true, {counts_out, counts_out ? 8 * T * npay : 0}));
-    DR_HIP(launch_query_decode_sum(w, npay, (uint32_t)T, (uint32_t)ntiles1, scale, dense_out, counts_out, s));
+    double pos = 0.0;  // a support's size is not known here: as many as it may have
+    for (const TInit &in : p.t) pos += in.r == R_NONZERO ? (double)in.d : in.r + cfg->fpr * (in.d - in.r);
+    DR_HIP(launch_query_decode_sum(w, npay, (uint32_t)T, (uint32_t)ntiles1, ntiles1 ? pos / (double)ntiles1 : 0.0,
+                                   scale, dense_out, counts_out, s));
     return DR_OK;
 }
 

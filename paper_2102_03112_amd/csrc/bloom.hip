@@ -2096,16 +2096,86 @@ __global__ __launch_bounds__(EMIT_THREADS) EMIT_WAVES_PER_EU(GEN) void k_emit(Wo
     }
 }
 
-// Summing emit pass: one block per tile of the dense gradient, whose sum is
-// kept in LDS.  A payload's positives in a tile are few (45 at 1%), and
-// listing and decoding them is a chain of dependent reads, so each of the
-// block's eight waves takes a payload: it lists the payload's positives,
-// decodes them into LDS, and then the block adds the payloads' values in order
-// p = 0, 1, ..., with a barrier between payloads so that every element sees
-// its terms in payload order.  The tile is then scaled and written once, zeros
-// included, by full-row stores.  Payloads with more than SUM_CAP positives in
-// the tile are listed and added by the whole block, one after the other, as
-// all were before (eight payloads of 25.6 M elements: 200 us, now 77).
+// Summing emit pass for payloads with many positives in a tile: one block per
+// tile of the dense gradient, whose sum is kept in LDS.  The payloads are added
+// in order p = 0, 1, ...: each payload's positives in the tile are listed (as in
+// k_emit), decoded one per thread, and added to their elements, with a barrier
+// between payloads so that every element sees its terms in payload order.  The
+// tile is then scaled and written once, zeros included, by full-row stores.
+__global__ __launch_bounds__(NTHREADS) void k_emit_sum_dense(Work w, QueryOut o) {
+    __shared__ uint32_t scratch[NWAVES + 1];
+    __shared__ uint32_t pw[TILE_WORDS];
+    __shared__ uint32_t pre[TILE_WORDS];
+    __shared__ uint16_t slot[TILE];
+    __shared__ float acc[TILE];
+    __shared__ float cf[EMIT_COEF];
+    __shared__ uint32_t kn[EMIT_KNOTS];
+    constexpr uint32_t GROUPS = TILE / (4 * NTHREADS);
+    for (uint32_t tile = blockIdx.x; tile < o.ntiles1; tile += gridDim.x) {
+        const uint32_t t = uni(tensor_of_tile(w, tile));  // payload 0's descriptor of the tensor
+        const uint32_t lt = tile - uni(w.td[t].in.tile0);
+        const uint32_t d = uni(w.td[t].in.d);
+        const uint64_t toff_el = uni(w.td[t].in.off);
+        for (uint32_t e = threadIdx.x; e < TILE; e += NTHREADS) acc[e] = 0.0f;
+        for (uint32_t p = 0; p < o.npay; ++p) {
+            const uint32_t v = p * o.ntens + t;
+            TDesc &td = w.td[v];
+            const uint32_t ptile = p * o.ntiles1 + tile;
+            const uint32_t word = threadIdx.x < TILE_WORDS ? w.pbits[(uint64_t)ptile * TILE_WORDS + threadIdx.x] : 0u;
+            const uint32_t q0 = uni(w.toff[ptile]);
+            bool ok = true;
+            RecordView rv = read_record(td.in.rec, td.in.rec_cap, d, &ok);
+            uniform_record(rv);
+            const uint32_t npos = uni(td.nv_dec);
+            const uint32_t ncoded = rv.policy == POLICY_P0 ? npos : min(rv.nv, npos);
+            uint32_t tot;
+            const uint32_t ex = block_excl_scan(__popc(word), scratch, &tot);
+            if (threadIdx.x < TILE_WORDS) {
+                pw[threadIdx.x] = word;
+                pre[threadIdx.x] = ex;
+            }
+            const float *cfu;
+            const uint32_t *knu;
+            stage_record(rv, cf, kn, &cfu, &knu);
+            __syncthreads();
+#pragma unroll
+            for (uint32_t u = 0; u < GROUPS; ++u) {
+                const uint32_t e0 = u * 4 * NTHREADS + threadIdx.x * 4;
+                const uint32_t wd = pw[e0 >> 5], sh = e0 & 31u;
+                const uint32_t nib = (wd >> sh) & 0xfu;
+                uint32_t r = pre[e0 >> 5] + __popc(sh ? wd << (32u - sh) : 0u);
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c)
+                    if ((nib >> c) & 1u) slot[r++] = (uint16_t)(e0 + c);
+            }
+            __syncthreads();
+            for (uint32_t x = threadIdx.x; x < tot; x += NTHREADS) {
+                const uint32_t vn = policy_slot(q0 + x, npos, ncoded, rv.policy, rv.seed);
+                acc[slot[x]] += positive_value<true>(rv, cfu, knu, vn, td, o.counts_out, v);
+            }
+            __syncthreads();  // pw, pre, slot, cf and kn are rewritten by the next payload
+        }
+        // scale and store the tile
+        float *dst = o.dense_out + toff_el + (uint64_t)lt * TILE;
+        const uint32_t n_el = min(TILE, d - lt * TILE);
+        if (n_el == TILE && ((uintptr_t)dst & 15u) == 0) {
+            for (uint32_t x = threadIdx.x; x < TILE / 4; x += NTHREADS) {
+                const float4 a = ((const float4 *)acc)[x];
+                ((float4 *)dst)[x] = make_float4(o.scale * a.x, o.scale * a.y, o.scale * a.z, o.scale * a.w);
+            }
+        } else {
+            for (uint32_t x = threadIdx.x; x < n_el; x += NTHREADS) dst[x] = o.scale * acc[x];
+        }
+        __syncthreads();  // acc is cleared for the next tile
+    }
+}
+
+// The same for payloads with few positives in a tile (45 at 1%), whose listing
+// and decoding is a chain of dependent reads: each of the block's eight waves
+// takes a payload, lists its positives and decodes them into LDS, and then the
+// block adds the payloads' values in order.  Payloads with more than SUM_CAP
+// positives in the tile are listed and added by the whole block, one after the
+// other (eight payloads of 25.6 M elements: 77 us; by k_emit_sum_dense 200).
 constexpr uint32_t SUM_THREADS = 512;
 constexpr uint32_t SUM_WAVES = SUM_THREADS / 64;  // payloads decoded together
 constexpr uint32_t SUM_CAP = 256;
@@ -2319,8 +2389,8 @@ hipError_t launch_emit_decode(const Work &w, float *dense_out, uint32_t *idx_out
     return hipGetLastError();
 }
 
-hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens, uint32_t ntiles1, float scale,
-                                   float *dense_out, uint64_t *counts_out, hipStream_t s) {
+hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens, uint32_t ntiles1, double pos_tile,
+                                   float scale, float *dense_out, uint64_t *counts_out, hipStream_t s) {
     QueryOut o{};
     o.counts_out = counts_out;
     o.dense_out = dense_out;
@@ -2330,8 +2400,23 @@ hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens,
     o.ntiles1 = ntiles1;
     // the pass also scans its tile counts (probe_scan)
     launch_probe<Q_SUM>(w, o, probe_grid(w), s);
-    k_emit_sum<<<resident_grid(k_emit_sum, SUM_THREADS, ntiles1), SUM_THREADS, 0, s>>>(w, o);
-    trace_mark(s, "k_emit_sum");
+    // k_emit_sum's waves without a payload idle, and a payload with more than
+    // SUM_CAP positives in a tile holds up the others; k_emit_sum_dense has more,
+    // smaller blocks.  So this is taken for a single payload and, where the tiles
+    // fill the chip twice, for more positives in a tile than 32 a payload, or
+    // nearly SUM_CAP (k_emit_sum_dense, k_emit_sum in us; 20 M elements, 3 and 8
+    // payloads): at 1% 71, 47 and 161, 63; at 5% 79, 87 and 189, 143; at 10% 104,
+    // 139 and 254, 331.  4 M, 3 payloads: at 2% 21.9, 20.1; at 4% 22.4, 24.3.  300 K, 8
+    // payloads at 25%: 61, 49.  2 M, one payload at 1%: 10, 12.
+    const bool dense = npay == 1 || (ntiles1 > 2u * (uint32_t)device_cus() &&
+                                     pos_tile > std::min<uint32_t>(npay * (SUM_CAP / SUM_WAVES), SUM_CAP * 7 / 8));
+    if (dense) {
+        k_emit_sum_dense<<<resident_grid(k_emit_sum_dense, NTHREADS, ntiles1), NTHREADS, 0, s>>>(w, o);
+        trace_mark(s, "k_emit_sum_dense");
+    } else {
+        k_emit_sum<<<resident_grid(k_emit_sum, SUM_THREADS, ntiles1), SUM_THREADS, 0, s>>>(w, o);
+        trace_mark(s, "k_emit_sum");
+    }
     return hipGetLastError();
 }
 

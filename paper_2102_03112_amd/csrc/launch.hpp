@@ -105,8 +105,9 @@ hipError_t launch_emit_decode(const Work &w, float *dense_out, uint32_t *idx_out
                               uint64_t *counts_out, bool general, hipStream_t s);
 // Several payloads of one tensor layout into one dense sum: the work's
 // tensors are payload-major (tensor t of payload p is p * ntens + t).
-hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens, uint32_t ntiles1, float scale,
-                                   float *dense_out, uint64_t *counts_out, hipStream_t s);
+// pos_tile: the positives that a payload is expected to have in a tile.
+hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens, uint32_t ntiles1, double pos_tile,
+                                   float scale, float *dense_out, uint64_t *counts_out, hipStream_t s);
 
 // valuefit.hip
 // the standalone calls' device counts: at most n_cap items are used, and

@@ -87,6 +87,14 @@ CASES = {
     # partitioned filters, one larger than the probe pass's LDS copy
     "partitioned_x3": (300_000, [0, 123_457, 300_000], (1, 100), 1e-3, 5, 8, 3, oracle.POLICY_P0, oracle.SEG_EQUAL,
                        oracle.FIT_POLY, oracle.LAYOUT_PARTITIONED),
+    # more tiles than twice the CUs and many positives in each: the whole block
+    # adds each payload in its turn
+    "dense_x3": (2_200_001, [0, 1_000_003, 2_200_001], (1, 4), 1e-2, 3, 600, 3, oracle.POLICY_P0),
+    "dense_support_x2": (2_200_001, [0, 2_200_001], None, 1e-2, 3, 4, 2, oracle.POLICY_P0),
+    "dense_chord_x2_p1": (2_200_001, [0, 2_200_001], (1, 8), 1e-2, 2, 6, 2, oracle.POLICY_RANDOM, oracle.SEG_CHORD,
+                          oracle.FIT_POLY),
+    # few positives on average, more than a wave's list holds in some tiles
+    "uneven_x9": (600_000, [0, 20_000, 600_000], (1, 12), 1e-2, 3, 4, 9, oracle.POLICY_P0),
     "partitioned_12m_x2": (12_000_000, [0, 12_000_000], (1, 100), 1e-3, 5, 8, 2, oracle.POLICY_P0, oracle.SEG_EQUAL,
                            oracle.FIT_POLY, oracle.LAYOUT_PARTITIONED),
 }
