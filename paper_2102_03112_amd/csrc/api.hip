@@ -708,12 +708,14 @@ void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t
 // Whether the probe pass's runs take several tensors (k_probe_many).  A block
 // runs over each tensor that its share of the tiles holds; a run costs it its
 // set-up and barriers, about what 7 steps of 512 indices take, and looking
-// tensors up costs every step about 1/26 of itself.  So runs are shared where
-// the block that is last to finish would have enough of them (receiver's call
-// in us, a run each against shared ones): 240 x (100 K, 1 K) elements, 5 runs
-// in 192 steps: 139 and 125; 300 x 40 K, 2 in 96: 79 and 73; 8 x (3 M, 1 K), 3
-// in 192: 102 and 100; 24 x (3 M, 1 K), 3 in 552: 211 and 212; 8 x (15 M, 1 M,
-// 1 K, 1 K), 4 in 984: 463 and 475; 12 M, 12 M and 100, 2 in 184: 136 and 145.
+// tensors up costs every step some percent.  So runs are shared where the block
+// that is last to finish would have extra ones enough for its steps, two at
+// least unless most blocks have them (receiver's call in us, a run each against
+// shared ones): 240 x (100 K, 1 K) elements, 4 extra runs, 192 steps: 139 and
+// 125; 24 x (2 M, 1 M, 4 K, 4 K), 3, 552 steps: 219 and 211; 8 x (3 M, 1 K), 2,
+// 192: 102 and 100; 24 x (3 M, 1 K), 2, 552: 211 and 212; 8 x (15 M, 1 M, 1 K,
+// 1 K), 3, 984: 463 and 475; 300 x 40 K, 1 in every block, 96: 79 and 73; 12 M,
+// 12 M and 100, 1 in two blocks, 184: 136 and 145.
 bool shared_runs(const std::vector<TInit> &t, uint64_t ntiles) {
     constexpr uint64_t RUN = 7, STEPS = TILE / 512;
     const uint64_t per = std::max<uint64_t>(1, ceil_div(ntiles, 256)), steps = per * STEPS;
@@ -726,7 +728,8 @@ bool shared_runs(const std::vector<TInit> &t, uint64_t ntiles) {
         if (in.tile0 % per != 0) ++runs;  // the share's first tile begins a run whatever starts there
         most = std::max(most, std::min(per, ntiles - block * per) * STEPS + RUN * runs);
     }
-    return most > steps + RUN && (most - steps - RUN) * 26 > steps;
+    const uint64_t extra = most > steps + RUN ? (most - steps - RUN) / RUN : 0;
+    return extra * 28 * RUN > steps && (extra >= 2 || t.size() * 2 >= ceil_div(ntiles, per));
 }
 
 // Descriptors and the zeroed regions; a query-only work has no histogram or
