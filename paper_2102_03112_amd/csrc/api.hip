@@ -662,19 +662,19 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     return DR_OK;
 }
 
-// The words in which the call's descriptors differ from the first, grouped
-// into columns of equal differences: first those that need 32 bits, then those
-// that 16 hold.  src: the descriptor word that each column follows.
-void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t> &src) {
-    a.base = t[0];
-    const uint32_t *base = (const uint32_t *)&a.base;
-    auto diff = [&](size_t c, uint32_t i) { return ((const uint32_t *)&t[c])[i] - base[i]; };
+// The words in which the call's descriptors (words: TINIT_WORDS each) differ from
+// the first, grouped into columns of equal differences: first those that need 32
+// bits, then those that 16 hold.  src: the descriptor word that each column follows.
+void init_columns(const std::vector<uint32_t> &words, InitArgs &a, std::vector<uint32_t> &src) {
+    const size_t T = words.size() / TINIT_WORDS;
+    memcpy(a.base, words.data(), sizeof a.base);
+    auto diff = [&](size_t c, uint32_t i) { return words[c * TINIT_WORDS + i] - a.base[i]; };
     std::vector<uint32_t> wide, narrow;
     uint32_t follows[TINIT_WORDS];  // the word whose column word i shares
     for (uint32_t i = 0; i < TINIT_WORDS; ++i) {
         follows[i] = TINIT_WORDS;
         bool same = true, small = true;
-        for (size_t c = 1; c < t.size(); ++c) {
+        for (size_t c = 1; c < T; ++c) {
             const uint32_t x = diff(c, i);
             same &= x == 0;
             small &= (int32_t)x == (int16_t)x;
@@ -683,7 +683,7 @@ void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t
         std::vector<uint32_t> &cols = small ? narrow : wide;
         for (uint32_t k : cols) {
             bool alike = true;
-            for (size_t c = 1; c < t.size() && alike; ++c) alike = diff(c, i) == diff(c, k);
+            for (size_t c = 1; c < T && alike; ++c) alike = diff(c, i) == diff(c, k);
             if (alike) {
                 follows[i] = k;
                 break;
@@ -753,21 +753,22 @@ hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, b
     if (extra.p && extra.words) z.z[z.n++] = extra;
     InitArgs a;
     memset(&a, 0, sizeof a);
-    std::vector<uint32_t> src;
-    init_columns(t, a, src);
+    std::vector<uint32_t> words(t.size() * TINIT_WORDS), src;
+    memcpy(words.data(), t.data(), 4 * words.size());
+    init_columns(words, a, src);
     const size_t per = a.row ? INIT_DATA / a.row : t.size();
-    const uint32_t *base = (const uint32_t *)&a.base;
     for (size_t f = 0; f < t.size(); f += per) {
         a.first = (uint32_t)f;
         a.count = (uint32_t)std::min<size_t>(per, t.size() - f);
         for (uint32_t c = 0; c < a.count; ++c) {
             uint32_t *row = a.data + c * a.row;
+            memset(row, 0, 4 * a.row);
             for (uint32_t k = 0; k < src.size(); ++k) {
-                const uint32_t x = ((const uint32_t *)&t[f + c])[src[k]] - base[src[k]];
+                const uint32_t x = words[(f + c) * TINIT_WORDS + src[k]] - a.base[src[k]], h = k - a.n32;
                 if (k < a.n32)
                     row[k] = x;
                 else
-                    ((int16_t *)(row + a.n32))[k - a.n32] = (int16_t)x;
+                    row[a.n32 + h / 2] |= (x & 0xffffu) << (16 * (h & 1u));
             }
         }
         hipError_t e = launch_init(w, a, z, s);

@@ -45,8 +45,8 @@ constexpr uint8_t INIT_SAME = 0xff;  // a word without a column
 struct InitArgs {
     uint32_t first, count;
     uint32_t n32, row;  // columns of whole words; words per tensor
-    TInit base;
-    uint8_t col[TINIT_WORDS];  // column k: word k (k < n32), or half-word k - n32 after those
+    uint32_t base[TINIT_WORDS];  // the call's first descriptor
+    uint8_t col[TINIT_WORDS];  // column k: word k (k < n32), or half-word k - n32 (low half first) after those
     uint32_t data[INIT_DATA];  // tensor first + c: [c row, (c + 1) row)
 };
 static_assert(INIT_DATA >= TINIT_WORDS && TINIT_WORDS < INIT_SAME, "any tensor fits a launch");

@@ -23,10 +23,12 @@ namespace dr {
 
 // Word i of the descriptor of the launch's tensor c.
 __device__ __forceinline__ uint32_t init_word(const InitArgs &a, uint32_t c, uint32_t i) {
-    const uint32_t k = a.col[i], base = ((const uint32_t *)&a.base)[i];
+    const uint32_t k = a.col[i], base = a.base[i];
     if (k == INIT_SAME) return base;
     const uint32_t *row = a.data + c * a.row;
-    return base + (k < a.n32 ? row[k] : (uint32_t)(int32_t)((const int16_t *)(row + a.n32))[k - a.n32]);
+    if (k < a.n32) return base + row[k];
+    const uint32_t h = k - a.n32;
+    return base + (uint32_t)(int32_t)(int16_t)(row[a.n32 + h / 2] >> (16 * (h & 1u)));
 }
 
 // Set-up: the blocks write the tensor descriptors of this launch, a word per
