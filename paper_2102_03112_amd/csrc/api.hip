@@ -662,19 +662,25 @@ dr_status plan_config(const dr_config *cfg, Plan &p, std::vector<uint64_t> &rec_
     return DR_OK;
 }
 
-// The words in which the call's descriptors (words: TINIT_WORDS each) differ from
-// the first, grouped into columns of equal differences: first those that need 32
-// bits, then those that 16 hold.  src: the descriptor word that each column follows.
-void init_columns(const std::vector<uint32_t> &words, InitArgs &a, std::vector<uint32_t> &src) {
-    const size_t T = words.size() / TINIT_WORDS;
-    memcpy(a.base, words.data(), sizeof a.base);
-    auto diff = [&](size_t c, uint32_t i) { return words[c * TINIT_WORDS + i] - a.base[i]; };
+// Word i of a descriptor.
+uint32_t init_word(const TInit &in, uint32_t i) {
+    uint32_t x;
+    memcpy(&x, (const unsigned char *)&in + 4 * i, 4);
+    return x;
+}
+
+// The words in which the call's descriptors differ from the first, grouped
+// into columns of equal differences: first those that need 32 bits, then those
+// that 16 hold.  src: the descriptor word that each column follows.
+void init_columns(const std::vector<TInit> &t, InitArgs &a, std::vector<uint32_t> &src) {
+    memcpy(a.base, &t[0], sizeof a.base);
+    auto diff = [&](size_t c, uint32_t i) { return init_word(t[c], i) - a.base[i]; };
     std::vector<uint32_t> wide, narrow;
     uint32_t follows[TINIT_WORDS];  // the word whose column word i shares
     for (uint32_t i = 0; i < TINIT_WORDS; ++i) {
         follows[i] = TINIT_WORDS;
         bool same = true, small = true;
-        for (size_t c = 1; c < T; ++c) {
+        for (size_t c = 1; c < t.size(); ++c) {
             const uint32_t x = diff(c, i);
             same &= x == 0;
             small &= (int32_t)x == (int16_t)x;
@@ -683,7 +689,7 @@ void init_columns(const std::vector<uint32_t> &words, InitArgs &a, std::vector<u
         std::vector<uint32_t> &cols = small ? narrow : wide;
         for (uint32_t k : cols) {
             bool alike = true;
-            for (size_t c = 1; c < T && alike; ++c) alike = diff(c, i) == diff(c, k);
+            for (size_t c = 1; c < t.size() && alike; ++c) alike = diff(c, i) == diff(c, k);
             if (alike) {
                 follows[i] = k;
                 break;
@@ -753,9 +759,8 @@ hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, b
     if (extra.p && extra.words) z.z[z.n++] = extra;
     InitArgs a;
     memset(&a, 0, sizeof a);
-    std::vector<uint32_t> words(t.size() * TINIT_WORDS), src;
-    memcpy(words.data(), t.data(), 4 * words.size());
-    init_columns(words, a, src);
+    std::vector<uint32_t> src;
+    init_columns(t, a, src);
     const size_t per = a.row ? INIT_DATA / a.row : t.size();
     for (size_t f = 0; f < t.size(); f += per) {
         a.first = (uint32_t)f;
@@ -764,7 +769,7 @@ hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, b
             uint32_t *row = a.data + c * a.row;
             memset(row, 0, 4 * a.row);
             for (uint32_t k = 0; k < src.size(); ++k) {
-                const uint32_t x = words[(f + c) * TINIT_WORDS + src[k]] - a.base[src[k]], h = k - a.n32;
+                const uint32_t x = init_word(t[f + c], src[k]) - a.base[src[k]], h = k - a.n32;
                 if (k < a.n32)
                     row[k] = x;
                 else

@@ -906,8 +906,8 @@ __device__ void probe_scan(const Work &w, const QueryOut &o, uint32_t t_begin, u
 //     and three below (0.06, 64 M: 585 and 576), and three at 0.5 and above.
 // With the partitioned layout the first parts, those of the first hashes, are
 // the ones LDS holds, and two are a group if it holds two parts and there are
-// 512 steps (25 M: 123 and 124; 60 M, two parts not held: 284 and 294; 24 x
-// 15 M: 1399 and 1258; 24 x 5 M: 441 and 410).  A filter that LDS holds whole needs no memory read, and two
+// 160 steps (12 M: 74 and 78; 25 M: 123 and 124, with 20 hashes the round trip
+// 418 and 394; 60 M, two parts not held: 284 and 294; 24 x 15 M: 1399 and 1258).  A filter that LDS holds whole needs no memory read, and two
 // hashes per group keep the lanes of a step busy, whatever the members (12 K
 // of 20 K elements: 54 and 49), but not for a tensor of a single step (three
 // of 100 elements: 24.8 and 26.8).
@@ -917,7 +917,7 @@ __device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, ui
     if (lim >= m_bits && !part) return d > QWAVE ? min(2u, max(k, 1u)) : 0u;
     // an m-bit filter of k hashes has about m ln 2 / k members
     if (k < 2 || 11ull * m_bits >= 2ull * k * d) return 0u;
-    if (part) return steps < 512 || (uint64_t)lim * k < 2ull * m_bits ? 0u : 2u;
+    if (part) return steps < 160 || (uint64_t)lim * k < 2ull * m_bits ? 0u : 2u;
     if (2ull * lim >= m_bits) return steps < (5ull * lim >= 3ull * m_bits ? 512u : 96u) ? 0u : min(3u, k);
     return min(10ull * lim >= m_bits ? 4u : 3u, k);
 }
