@@ -346,7 +346,13 @@ __device__ __forceinline__ bool bs_scan(uint32_t *h, uint32_t n, uint32_t *scrat
             h[b + u] = at;
             at += v[u];
         }
-    return __syncthreads_or(most > BS_BIN_MAX) != 0;
+    const bool big = ballot(most > BS_BIN_MAX) != 0;
+    if ((threadIdx.x & 63u) == 0) scratch[threadIdx.x >> 6] = big;
+    __syncthreads();
+    uint32_t any = 0;
+    for (uint32_t q = 0; q < NT / 64; ++q) any |= scratch[q];
+    __syncthreads();
+    return any != 0;
 }
 
 __device__ __forceinline__ void bs_range(uint64_t &lo, uint64_t &hi, uint64_t *lohi, uint32_t nw) {
@@ -567,7 +573,7 @@ __device__ __forceinline__ void bs_sort_lds(const uint64_t (&x)[CAP / NT], uint3
     if (threadIdx.x == 0) l.h2[n] = n;
     __syncthreads();
     bs_place<NT, E>(x, at, n, l.out, 0, l.h2, cut ? BS_BIN_CUT : BS_BIN_MAX, l.heavy[0]);
-    for (uint32_t r = 0; l.heavy[r & 1u][0] > 0; ++r) {
+    for (uint32_t r = 0; __builtin_expect(l.heavy[r & 1u][0] > 0, 0); ++r) {
         if (r == BS_REFINE) {
             bs_network<NT>(l.out, n);
             return;

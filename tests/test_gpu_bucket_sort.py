@@ -1,6 +1,10 @@
 """The bucket sort of the values: one bucket, the edges of one and of several,
-ties of every kind, and a bucket that outgrows its room.  Reorder map and
-coefficients against the oracle."""
+ties of every kind, and a bucket that outgrows its room.  The reorder map against
+the oracle's, and the sorted values, which the fit reads, by the coefficients of a
+constant over each of many short runs."""
+import math
+import re
+
 import numpy as np
 import pytest
 
@@ -55,33 +59,58 @@ CASES = [(n, "normal") for n in SIZES] + [(n, "ulps") for n in (CAP, 30_000, 512
 CASES += [(n, k) for n in (CAP, 30_000) for k in ("equal", "zeros", "coarse", "sorted", "wide")]
 
 
-@pytest.mark.parametrize("n,kind", CASES + [(30_000, "outgrown")])
-def test_reorder_map(n, kind):
+def encode(v, degree, n_seg, ws):
+    """The device's reorder map and coefficients."""
     import torch
 
+    n = v.size
+    nd = torch.tensor([n], dtype=torch.int64, device="cuda")
+    coef = torch.zeros(n_seg * (degree + 1), dtype=torch.float32, device="cuda")
+    sigma = torch.zeros((n * B.sigma_bits(n) + 31) // 32, dtype=torch.int32, device="cuda")
+    B.curvefit_encode(dev_tensor(v), nd, n, degree, n_seg, coef, sigma, ws)
+    sync()
+    return host(sigma).view(np.uint32), host(coef)
+
+
+def check_sorted_values(v, coef):
+    """A run's constant is the mean of its sorted values, summed in double and
+    rounded once: an ulp from the mean of their exact sum, and the sums' own
+    rounding, at most (values - 1) 2^-53 of the sum of magnitudes each way."""
+    order = np.sort(v.astype(np.float64))[::-1]
+    n, runs = order.size, min(coef.size, order.size)
+    at = np.arange(runs + 1, dtype=np.int64) * n // runs
+    for s in range(runs):
+        x = order[at[s]:at[s + 1]]
+        mean = math.fsum(x) / x.size
+        tol = float(np.spacing(np.float32(abs(mean)))) + 4 * x.size * 2.0 ** -53 * float(np.abs(x).sum()) / x.size
+        assert abs(float(coef[s]) - mean) <= tol, (s, float(coef[s]), mean, tol)
+
+
+@pytest.mark.parametrize("n,kind", CASES + [(30_000, "outgrown")])
+def test_reorder_map(n, kind):
     log(f"sort n={n} kind={kind}")
     v = values(kind, n, np.random.default_rng(n)).astype(np.float32)
-    ref = oracle.curvefit_encode(v, 3, 4)
-    nd = torch.tensor([n], dtype=torch.int64, device="cuda")
-    coef = torch.zeros(16, dtype=torch.float32, device="cuda")
-    sigma = torch.zeros((n * B.sigma_bits(n) + 31) // 32, dtype=torch.int32, device="cuda")
-    B.curvefit_encode(dev_tensor(v), nd, n, 3, 4, coef, sigma, workspace(8 * n))
-    sync()
-    np.testing.assert_array_equal(host(sigma).view(np.uint32), ref.sigma)
+    ws = workspace(8 * n)
+    sigma, coef = encode(v, 0, 4096, ws)
+    np.testing.assert_array_equal(sigma, oracle.curvefit_encode(v, 3, 4).sigma)
+    check_sorted_values(v, coef)
 
 
 def test_workspace_without_room_for_buckets():
-    """The exact workspace of so many values: the radix sort instead."""
-    import torch
-
+    """The exact workspace that the call asks for: the radix sort instead."""
     n = 50_000
     v = np.random.default_rng(1).standard_normal(n).astype(np.float32)
-    nd = torch.tensor([n], dtype=torch.int64, device="cuda")
-    coef = torch.zeros(16, dtype=torch.float32, device="cuda")
-    sigma = torch.zeros((n * B.sigma_bits(n) + 31) // 32, dtype=torch.int32, device="cuda")
-    B.curvefit_encode(dev_tensor(v), nd, n, 3, 4, coef, sigma, B.workspace(n))
-    sync()
-    np.testing.assert_array_equal(host(sigma).view(np.uint32), oracle.curvefit_encode(v, 3, 4).sigma)
+    with pytest.raises(B.DeepReduceError) as e:
+        encode(v, 0, 4096, B.workspace(n)[:256])
+    need = int(re.search(r"need (\d+)", str(e.value)).group(1))
+    names = []
+    for size in (need, B.workspace_bytes(n)):
+        B.trace_begin()
+        sigma, coef = encode(v, 0, 4096, B.workspace(n)[:size])
+        names.append(set(B.trace_end()))
+        np.testing.assert_array_equal(sigma, oracle.curvefit_encode(v, 3, 4).sigma)
+        check_sorted_values(v, coef)
+    assert "k_sort_pass" in names[0] and "k_bsort_bucket" in names[1]
 
 
 @pytest.mark.parametrize("source", [B.VALUES_DENSE, B.VALUES_SPARSE], ids=["dense", "sparse"])
