@@ -739,8 +739,8 @@ __device__ __forceinline__ RecordView query_filter(const Work &w, const QueryOut
 // the emptying loop per kind of filter): with three copies a 37 k element
 // tensor's pass took 31 us instead of 19, in instruction fetches.
 // Against testing one hash at a time (probe_single; sender's, receiver's pass
-// in us): resnet50_25m 157, 179 -> 128, 146; vgg16_138m 479, 536 -> 401, 480;
-// transformer_355m_x24 1250-1510, 2000 -> 1003, 1408.
+// in us): resnet50_25m 155, 179 -> 124, 144; vgg16_138m 480, 539 -> 398, 473;
+// transformer_355m_x24 1509, 1987 -> 1030, 1434.
 constexpr uint32_t RUN_TILES = 512;  // most tiles per run (LDS tile counters)
 constexpr uint32_t RUN_TENSORS = 32;  // most tensors per run
 
