@@ -894,23 +894,25 @@ __device__ void probe_scan(const Work &w, const QueryOut &o, uint32_t t_begin, u
 // first two groups once more for the members, against memory reads, and works
 // on several steps at once.  So it pays where most indices are no members, LDS
 // holds a smaller share of the filter, and the block's share of the tiles (in
-// steps) is long enough for full windows.  Receiver's whole call in us, one hash at a time against the
-// group taken, by what decides:
+// steps) is long enough for full windows.  Receiver's whole call in us, one
+// hash at a time against the group taken, by what decides:
 //   members, an eighth of the indices or more (estimated from the filter's
 //     size): 0.42 M elements, 60%: 62 and 68; 4 M, 25%: 106 and 110
-//   share of 0.6 and more, fewer than 512 steps: 8 M elements, 1%: 56
-//     and 66; 32 M: 132 and 136; 64 M equal; 256 M: 816 and 795
-//   share of 0.5, fewer than 96: 8 M: 66 and 69; 16 M: 98 and 95; 256 M: 970 and 815
-//   smaller shares: 0.31 (25.6 M): 176 and 145; 0.13 (60 M): 483 and 427;
-//     0.08 (100 M): 825 and 791.  There four hashes down to a share of a tenth
-//     and three below (0.06, 64 M: 585 and 576), and three at 0.5 and above.
+//   share of 0.6 and more, fewer than 512 steps: 8 M elements: 56 and 66;
+//     32 M: 132 and 136; 64 M equal; 256 M: 816 and 795
+//   share of 0.5, fewer than 96 steps: 8 M: 66 and 69; 16 M: 98 and 95;
+//     256 M: 970 and 815
+//   smaller shares, groups of four: 0.31 (25.6 M): 176 and 145; 0.13 (60 M):
+//     483 and 427.  Below a tenth, and at 0.5 and above, three: 0.08 (100 M)
+//     825 and 791; 0.06 (64 M) 583 and 576, with four 585.
 // With the partitioned layout the first parts, those of the first hashes, are
 // the ones LDS holds, and two are a group if it holds two parts and there are
 // 160 steps (12 M: 74 and 78; 25 M: 123 and 124, with 20 hashes the round trip
-// 418 and 394; 60 M, two parts not held: 284 and 294; 24 x 15 M: 1399 and 1258).  A filter that LDS holds whole needs no memory read, and two
-// hashes per group keep the lanes of a step busy, whatever the members (12 K
-// of 20 K elements: 54 and 49), but not for a tensor of a single step (three
-// of 100 elements: 24.8 and 26.8).
+// 418 and 394; 60 M, two parts not held: 284 and 294; 24 x 15 M: 1399 and
+// 1258).  A filter that LDS holds whole needs no memory read, and two hashes
+// per group keep the lanes of a step busy, whatever the members (12 K of 20 K
+// elements: 54 and 49), but not for a tensor of a single step (three of 100
+// elements: 24.8 and 26.8).
 __device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout, uint32_t d,
                                                  uint32_t steps) {
     const bool part = layout == LAYOUT_PARTITIONED;
@@ -1391,8 +1393,8 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
 }
 
 // The same with runs of as many whole tensors as the LDS copy has room for,
-// so that a model's small layers share a run's set-up and barriers
-// (where the host's plan finds that it pays).  A run's tensors are held one per lane.
+// so that a model's small layers share a run's set-up and barriers (where the
+// host's plan finds that it pays).  A run's tensors are held one per lane.
 template <int MODE>
 __global__ __launch_bounds__(PB_THREADS) void k_probe_many(Work w, QueryOut o) {
     __shared__ uint32_t fc[FC_WORDS + 1];
@@ -2406,8 +2408,8 @@ hipError_t launch_query_decode_sum(const Work &w, uint32_t npay, uint32_t ntens,
     // fill the chip twice, for more positives in a tile than 32 a payload, or
     // nearly SUM_CAP (k_emit_sum_dense, k_emit_sum in us; 20 M elements, 3 and 8
     // payloads): at 1% 71, 47 and 161, 63; at 5% 79, 87 and 189, 143; at 10% 104,
-    // 139 and 254, 331.  4 M, 3 payloads: at 2% 21.9, 20.1; at 4% 22.4, 24.3.  300 K, 8
-    // payloads at 25%: 61, 49.  2 M, one payload at 1%: 10, 12.
+    // 139 and 254, 331.  4 M, 3 payloads: at 2% 21.9, 20.1; at 4% 22.4, 24.3.
+    // 300 K, 8 payloads at 25%: 61, 49.  2 M, one payload at 1%: 10, 12.
     const bool dense = npay == 1 || (ntiles1 > 2u * (uint32_t)device_cus() &&
                                      pos_tile > std::min<uint32_t>(npay * (SUM_CAP / SUM_WAVES), SUM_CAP * 7 / 8));
     if (dense) {

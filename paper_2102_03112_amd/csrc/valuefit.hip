@@ -346,6 +346,7 @@ __device__ __forceinline__ bool bs_scan(uint32_t *h, uint32_t n, uint32_t *scrat
             h[b + u] = at;
             at += v[u];
         }
+    // (__syncthreads_or took the splitters' launch 0.9 us more)
     const bool big = ballot(most > BS_BIN_MAX) != 0;
     if ((threadIdx.x & 63u) == 0) scratch[threadIdx.x >> 6] = big;
     __syncthreads();
@@ -378,10 +379,11 @@ __device__ __forceinline__ uint32_t bs_bin(uint64_t x, uint64_t lo, double scale
 
 // Puts the pairs x[u] (element u NT + thread of n) into order within their
 // bins, from out[base] on: at[u] is bin << 16 | place in it, h the bins' first
-// pairs and the end.  A pair's rank in a bin of up to `limit` is found by comparing; a fuller
-// bin's pairs are left as they come and the bin goes to the list heavy[1 ..],
-// counted in heavy[0].  (Sorting a bin by insertion, a thread per bin, took
-// stages_4m's launch, whose values repeat a few times each, from 42 to 98 us.)
+// pairs and the end.  A pair's rank in a bin of up to `limit` is found by
+// comparing; a fuller bin's pairs are left as they come and the bin goes to the
+// list heavy[1 ..], counted in heavy[0].  (Sorting a bin by insertion, a thread
+// per bin, took stages_4m's launch, whose values repeat a few times each, from
+// 42 to 98 us.)
 template <uint32_t NT, uint32_t E>
 __device__ __forceinline__ void bs_place(const uint64_t (&x)[E], uint32_t (&at)[E], uint32_t n, uint64_t *out,
                                          uint32_t base, const uint32_t *h, uint32_t limit, uint32_t *heavy) {
