@@ -738,6 +738,18 @@ bool shared_runs(const std::vector<TInit> &t, uint64_t ntiles) {
     return extra * 28 * RUN > steps && (extra >= 2 || t.size() * 2 >= ceil_div(ntiles, per));
 }
 
+// Whether the probe pass tests every filter of the plan one hash at a time (a
+// record that holds another filter than planned is tested so all the same).
+bool single_hashes(const std::vector<TInit> &t, uint64_t ntiles) {
+    const uint32_t steps = (uint32_t)std::min<uint64_t>(ceil_div(ntiles, 256) * (TILE / QWAVE), 0xffffffffu);
+    for (const TInit &in : t) {
+        if (in.m_words_in == 0) return false;  // a support's filter: its size is known on the device
+        const uint32_t lim = 32u * std::min(in.m_words_in, FC_WORDS);
+        if (probe_hashes(32u * in.m_words_in, in.k, lim, in.layout, in.d, steps) != 0) return false;
+    }
+    return true;
+}
+
 // Descriptors and the zeroed regions; a query-only work has no histogram or
 // sort regions, and `extra` (words) is a caller's buffer to clear as well.
 hipError_t run_init(const Work &w, const std::vector<TInit> &t, hipStream_t s, bool query_only = false,
@@ -834,6 +846,7 @@ dr_status encode_prepare(const float *g, const dr_config *cfg, uint8_t *payload,
     e.w = e.p.carve.view((uint8_t *)ws);
     e.w.counts_out = counts_out;
     e.w.shared = shared_runs(e.p.t, e.p.carve.ntiles);
+    e.w.single = single_hashes(e.p.t, e.p.carve.ntiles);
     return DR_OK;
 }
 
@@ -899,6 +912,7 @@ dr_status decode_prepare(const uint8_t *payload, const dr_config *cfg, float *de
     if (!dense_out && cfg->offsets_h[cfg->n_tensors] > 0) return fail(DR_EINVAL, "dense_out is null");
     if (!ws_ok(ws, ws_bytes, dd.p.carve.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", dd.p.carve.bytes);
+    const bool single = single_hashes(dd.p.t, dd.p.carve.ntiles);
     for (size_t t = 0; t < dd.p.t.size(); ++t) {
         dd.p.t[t].rec_cap = dd.rec_off[t + 1] - dd.rec_off[t];
         dd.p.t[t].rec = const_cast<uint8_t *>(payload) + dd.rec_off[t];
@@ -906,6 +920,7 @@ dr_status decode_prepare(const uint8_t *payload, const dr_config *cfg, float *de
     }
     dd.w = dd.p.carve.view((uint8_t *)ws);
     dd.w.shared = shared_runs(dd.p.t, dd.p.carve.ntiles);
+    dd.w.single = single;
     dd.dense_out = dense_out;
     dd.idx_out = idx_out;
     dd.val_out = val_out;
@@ -1027,6 +1042,7 @@ dr_status roundtrip_impl(const float *g, const dr_config *cfg, uint8_t *payload,
         // the sender selects
         dd.w = qc.view((uint8_t *)ws + qoff);
         dd.w.shared = e.w.shared;
+        dd.w.single = e.w.single;
         dd.w.qlist = e.w.qlist;
         dd.w.qbkt = e.w.qbkt;
         dd.w.qtab = e.w.qtab;
@@ -1175,6 +1191,7 @@ dr_status decode_sum_impl(const uint8_t *const *payloads, uint32_t npay, const d
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", c.bytes);
     Work w = c.view((uint8_t *)ws);
     w.shared = shared_runs(vt, c.ntiles);
+    w.single = single_hashes(p.t, c.ntiles);
     trace_call(s);
     DR_HIP(run_init(w, vt, s, true, {counts_out, counts_out ? 8 * T * npay : 0}));
     double pos = 0.0;  // a support's size is not known here: as many as it may have
@@ -1656,7 +1673,8 @@ dr_status dr_bloom_decode(const uint32_t *bits, uint64_t m_bits, uint32_t k, uin
     p.carve.plan();
     if (!ws_ok(ws, ws_bytes, p.carve.bytes))
         return fail(DR_EINVAL, "workspace too small or not 256-byte aligned (need %zu)", p.carve.bytes);
-    const Work w = p.carve.view((uint8_t *)ws);
+    Work w = p.carve.view((uint8_t *)ws);
+    w.single = single_hashes(p.t, p.carve.ntiles);
     trace_call(s);
     DR_HIP(run_init(w, p.t, s));
     DR_HIP(launch_query_plain(w, idx_out, cap, n_out, persist_grid(4), s));

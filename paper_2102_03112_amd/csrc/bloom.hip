@@ -684,13 +684,11 @@ __device__ __forceinline__ uint32_t sigma_get(const uint32_t *sig, uint64_t bit,
     return b == 32u ? (uint32_t)v : (uint32_t)(v & ((1ull << b) - 1ull));
 }
 
-constexpr uint32_t QWAVE = 512;              // indices per wave per step (an eighth of a tile)
 constexpr uint32_t PB_THREADS = 1024;        // probe block: 16 waves, one block per CU
 constexpr uint32_t PB_WAVES = PB_THREADS / 64;
 constexpr uint32_t PB_TILES = PB_WAVES * QWAVE / TILE;  // tiles one block probes per step
 constexpr uint32_t WSTEPS = 4;               // steps per window, the unit a wave takes
 constexpr uint32_t QCAP = QWAVE;             // entries of a wave's queue
-constexpr uint32_t FC_WORDS = 35072;         // filter words kept in LDS (137 KiB)
 
 // The filter a tile is probed against: the sender's freshly built filter,
 // the caller's (plain decode), or the payload record's (receiver).
@@ -887,41 +885,6 @@ __device__ void probe_scan(const Work &w, const QueryOut &o, uint32_t t_begin, u
         for (uint32_t q = 0; q < PB_WAVES; ++q) carry = lds[PB_WAVES + q] ? lds[q] : carry + lds[q];
         __syncthreads();  // lds is rewritten by the next chunk
     }
-}
-
-// Hashes per group, 2 to 4 and at most k, or 0: one hash at a time.  A group
-// trades vector work and LDS reads, J hashes for every index and those of the
-// first two groups once more for the members, against memory reads, and works
-// on several steps at once.  So it pays where most indices are no members, LDS
-// holds a smaller share of the filter, and the block's share of the tiles (in
-// steps) is long enough for full windows.  Receiver's whole call in us, one
-// hash at a time against the group taken, by what decides:
-//   members, an eighth of the indices or more (estimated from the filter's
-//     size): 0.42 M elements, 60%: 62 and 68; 4 M, 25%: 106 and 110
-//   share of 0.6 and more, fewer than 512 steps: 8 M elements: 56 and 66;
-//     32 M: 132 and 136; 64 M equal; 256 M: 816 and 795
-//   share of 0.5, fewer than 96 steps: 8 M: 66 and 69; 16 M: 98 and 95;
-//     256 M: 970 and 815
-//   smaller shares, groups of four: 0.31 (25.6 M): 176 and 145; 0.13 (60 M):
-//     483 and 427.  Below a tenth, and at 0.5 and above, three: 0.08 (100 M)
-//     825 and 791; 0.06 (64 M) 583 and 576, with four 585.
-// With the partitioned layout the first parts, those of the first hashes, are
-// the ones LDS holds, and two are a group if it holds two parts and there are
-// 160 steps (12 M: 74 and 78; 25 M: 123 and 124, with 20 hashes the round trip
-// 418 and 394; 60 M, two parts not held: 284 and 294; 24 x 15 M: 1399 and
-// 1258).  A filter that LDS holds whole needs no memory read, and two hashes
-// per group keep the lanes of a step busy, whatever the members (12 K of 20 K
-// elements: 54 and 49), but not for a tensor of a single step (three of 100
-// elements: 24.8 and 26.8).
-__device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout, uint32_t d,
-                                                 uint32_t steps) {
-    const bool part = layout == LAYOUT_PARTITIONED;
-    if (lim >= m_bits && !part) return d > QWAVE ? min(2u, max(k, 1u)) : 0u;
-    // an m-bit filter of k hashes has about m ln 2 / k members
-    if (k < 2 || 11ull * m_bits >= 2ull * k * d) return 0u;
-    if (part) return steps < 160 || (uint64_t)lim * k < 2ull * m_bits ? 0u : 2u;
-    if (2ull * lim >= m_bits) return steps < (5ull * lim >= 3ull * m_bits ? 512u : 96u) ? 0u : min(3u, k);
-    return min(10ull * lim >= m_bits ? 4u : 3u, k);
 }
 
 // A tensor's filter as the probe pass's waves read it: the words of the bits
@@ -1260,7 +1223,7 @@ __device__ __forceinline__ void probe_single(const ProbeFilter &f, uint16_t *me,
 // A wave's window: ns steps from step `st` of a tile of the tensor at tile0,
 // d elements from `off`.  Writes its words of the positives bitmap and, for
 // the receiver, its zeros; returns its positives.
-template <int MODE>
+template <int MODE, bool SINGLE>
 __device__ __forceinline__ uint32_t probe_take(const Work &w, const QueryOut &o, const ProbeFilter &f, bool pre,
                                                bool part, bool all_lds, uint32_t J, uint64_t off, uint32_t tile0,
                                                uint32_t d, uint32_t tile, uint32_t st, uint32_t ns, uint16_t *me,
@@ -1283,11 +1246,11 @@ __device__ __forceinline__ uint32_t probe_take(const Work &w, const QueryOut &o,
         for (uint32_t s0 = 0; s0 < nvalid; s0 += QWAVE) zero_step(dz, s0, nvalid);
     if (!pre) {
         if (f.k > 0 && nvalid > 0) {
-            if (all_lds && !part && J != 0)
+            if (!SINGLE && all_lds && !part && J != 0)
                 probe_window<MODE, PK_LDS>(f, me, mw, wbase, nvalid, dz);
-            else if (J != 0 && !part)
+            else if (!SINGLE && J != 0 && !part)
                 probe_window<MODE, PK_STANDARD>(f, me, mw, wbase, nvalid, dz);
-            else if (J != 0)
+            else if (!SINGLE && J != 0)
                 probe_window<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
             else if (part)
                 probe_single<MODE, PK_PARTITIONED>(f, me, mw, wbase, nvalid, dz);
@@ -1317,8 +1280,9 @@ struct Windows {
     }
 };
 
-template <int MODE>
-__global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
+// SINGLE: every filter one hash at a time.
+template <int MODE, bool SINGLE>
+__device__ __forceinline__ void probe_runs(const Work &w, const QueryOut &o) {
     __shared__ uint32_t fc[FC_WORDS + 1];
     __shared__ uint16_t qe[PB_WAVES][QCAP];
     __shared__ uint32_t lw[PB_WAVES][WSTEPS * QWAVE / 32];
@@ -1362,7 +1326,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
         const uint32_t d = td.in.d, tile0 = td.in.tile0, k = uni(rv.k);
         const bool part = uni(rv.layout) == LAYOUT_PARTITIONED;
         const uint32_t lim = uni(fcw * 32u);
-        const uint32_t J = uni(probe_hashes(rv.m_bits, k, lim, rv.layout, d, (t_end - t_begin) * QPT));
+        const uint32_t J = SINGLE ? 0u : uni(probe_hashes(rv.m_bits, k, lim, rv.layout, d, (t_end - t_begin) * QPT));
         const ProbeFilter f{fc, ps, buffer_view(rv.bits, rv.m_bits / 8u), uni(rv.m_bits), k, lim, J};
         uint16_t *me = qe[wv];
         uint32_t *mw = lw[wv];
@@ -1374,8 +1338,8 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
             if (qi >= win.count()) break;
             const uint32_t ns = win.steps(qi), st = win.first(qi);
             const uint32_t tile = rb + st / QPT;
-            const uint32_t total = probe_take<MODE>(w, o, f, pre, part, lim >= f.m_bits, J, td.in.off, tile0, d, tile,
-                                                    st % QPT, ns, me, mw);
+            const uint32_t total = probe_take<MODE, SINGLE>(w, o, f, pre, part, lim >= f.m_bits, J, td.in.off, tile0, d,
+                                                            tile, st % QPT, ns, me, mw);
             if (lane == 0) atomicAdd(&tcl[st / QPT], total);
             // the wave reconverges here, before the next window's ticket:
             // without it the compiler merged this lane-0 branch with
@@ -1390,6 +1354,20 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
     }
     __syncthreads();  // the block's tile counts are written; fc is free
     probe_scan<MODE>(w, o, t_begin, t_end, fc);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(PB_THREADS) void k_probe(Work w, QueryOut o) {
+    probe_runs<MODE, false>(w, o);
+}
+
+// For calls whose filters the host knows to be tested one hash at a time: with
+// the groups' code beside it, which is never run, the pass is 0.5 to 1.4 us
+// longer (registers and instruction fetches; a receiver's call of 8 M elements
+// 56.4 and 55.0, a query of 4 M with 20 hashes 40.8 and 39.7).
+template <int MODE>
+__global__ __launch_bounds__(PB_THREADS) void k_probe_single(Work w, QueryOut o) {
+    probe_runs<MODE, true>(w, o);
 }
 
 // The same with runs of as many whole tensors as the LDS copy has room for,
@@ -1507,7 +1485,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_probe_many(Work w, QueryOut o) {
             const uint64_t off = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(v_off[1], sl) << 32) |
                                  (uint32_t)__builtin_amdgcn_readlane(v_off[0], sl);
             const uint32_t total =
-                probe_take<MODE>(w, o, f, pre, part, all_lds, J0, off, __builtin_amdgcn_readlane(v_tile0, sl),
+                probe_take<MODE, false>(w, o, f, pre, part, all_lds, J0, off, __builtin_amdgcn_readlane(v_tile0, sl),
                                  __builtin_amdgcn_readlane(v_d, sl), tile, st % QPT, ns, me, mw);
             if (lane == 0) atomicAdd(&tcl[st / QPT], total);
             __builtin_amdgcn_wave_barrier();  // the wave reconverges here, as in k_probe
@@ -2299,14 +2277,22 @@ static int probe_grid(const Work &w) {
 
 template <int MODE>
 static void launch_probe(const Work &w, const QueryOut &o, int grid, hipStream_t s) {
-    if (w.shared)
-        k_probe_many<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
+    static const char *const names[3][4] = {
+        {"k_probe<Q_ENCODE>", "k_probe<Q_PLAIN>", "k_probe<Q_DECODE>", "k_probe<Q_SUM>"},
+        {"k_probe_single<Q_ENCODE>", "k_probe_single<Q_PLAIN>", "k_probe_single<Q_DECODE>", "k_probe_single<Q_SUM>"},
+        {"k_probe_many<Q_ENCODE>", "", "k_probe_many<Q_DECODE>", "k_probe_many<Q_SUM>"}};
+    if constexpr (MODE != Q_PLAIN) {  // (which has one tensor)
+        if (w.shared) {
+            k_probe_many<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
+            trace_mark(s, names[2][MODE]);
+            return;
+        }
+    }
+    if (w.single)
+        k_probe_single<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
     else
         k_probe<MODE><<<grid, PB_THREADS, 0, s>>>(w, o);
-    static const char *const names[2][4] = {
-        {"k_probe<Q_ENCODE>", "k_probe<Q_PLAIN>", "k_probe<Q_DECODE>", "k_probe<Q_SUM>"},
-        {"k_probe_many<Q_ENCODE>", "", "k_probe_many<Q_DECODE>", "k_probe_many<Q_SUM>"}};
-    trace_mark(s, names[w.shared ? 1 : 0][MODE]);
+    trace_mark(s, names[w.single ? 1 : 0][MODE]);
 }
 
 hipError_t launch_query_encode(const Work &w, const float *g, int grid_persist, uint64_t *counts_out, hipStream_t s,
@@ -2356,8 +2342,7 @@ hipError_t launch_query_plain(const Work &w, uint32_t *idx_out, uint64_t cap, ui
     o.cap = cap;
     o.n_out = n_out;
     // the pass also scans its tile counts (probe_scan)
-    k_probe<Q_PLAIN><<<probe_grid(w), PB_THREADS, 0, s>>>(w, o);  // (one tensor)
-    trace_mark(s, "k_probe<Q_PLAIN>");
+    launch_probe<Q_PLAIN>(w, o, probe_grid(w), s);
     k_emit<Q_PLAIN><<<resident_grid(k_emit<Q_PLAIN>, EMIT_THREADS, w.ntiles_total), EMIT_THREADS, 0, s>>>(w, o);
     trace_mark(s, "k_emit<Q_PLAIN>");
     return hipGetLastError();

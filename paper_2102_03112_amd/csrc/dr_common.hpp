@@ -246,6 +246,46 @@ constexpr uint32_t FLAG_CAPACITY = 8u;       // a device-side capacity was excee
 constexpr uint32_t FLAG_STALLED = 16u;       // a bounded wait gave up (internal error)
 constexpr uint32_t PSTAT_MAX = 4096;         // probe pass blocks with a look-back entry (at most)
 
+constexpr uint32_t QWAVE = 512;  // indices per wave per step (an eighth of a tile)
+constexpr uint32_t FC_WORDS = 35072;  // filter words kept in LDS (137 KiB)
+
+// Hashes per group, 2 to 4 and at most k, or 0: one hash at a time.  A group
+// trades vector work and LDS reads, J hashes for every index and those of the
+// first two groups once more for the members, against memory reads, and works
+// on several steps at once.  So it pays where most indices are no members, LDS
+// holds a smaller share of the filter, and the block's share of the tiles (in
+// steps) is long enough for full windows.  Receiver's whole call in us, one
+// hash at a time against the group taken, by what decides:
+//   members, an eighth of the indices or more (estimated from the filter's
+//     size): 0.42 M elements, 60%: 62 and 68; 4 M, 25%: 106 and 110
+//   share of 0.6 and more, fewer than 512 steps: 8 M elements: 56 and 66;
+//     32 M: 132 and 136; 64 M equal; 256 M: 816 and 795
+//   share of 0.5, fewer than 96 steps: 8 M: 66 and 69; 16 M: 98 and 95;
+//     256 M: 970 and 815
+//   smaller shares, groups of four: 0.31 (25.6 M): 176 and 145; 0.13 (60 M):
+//     483 and 427.  Below a tenth, and at 0.5 and above, three: 0.08 (100 M)
+//     825 and 791; 0.06 (64 M) 583 and 576, with four 585.
+// With the partitioned layout the first parts, those of the first hashes, are
+// the ones LDS holds, and two are a group if it holds two parts of four or more
+// and there are 160 steps (25 M, three parts: 116 and 127; ten: 123 and 124;
+// twenty, the round trip: 418 and 394; 12 M: 74 and 78; 60 M, two parts not
+// held: 284 and 294; 24 x 15 M: 1399 and 1258).  A filter that LDS holds whole
+// needs no memory read, and two hashes per group keep the lanes of a step busy,
+// whatever the members (12 K of 20 K elements: 54 and 49), but not for a tensor
+// of a single step (three of 100
+// elements: 24.8 and 26.8).
+__host__ __device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout, uint32_t d,
+                                                 uint32_t steps) {
+    const bool part = layout == LAYOUT_PARTITIONED;
+    if (lim >= m_bits && !part) return d > QWAVE ? (k > 1 ? 2u : 1u) : 0u;
+    // an m-bit filter of k hashes has about m ln 2 / k members
+    if (k < 2 || 11ull * m_bits >= 2ull * k * d) return 0u;
+    if (part) return steps < 160 || k < 4 || (uint64_t)lim * k < 2ull * m_bits ? 0u : 2u;
+    if (2ull * lim >= m_bits) return steps < (5ull * lim >= 3ull * m_bits ? 512u : 96u) ? 0u : (k < 3 ? k : 3u);
+    const uint32_t J = 10ull * lim >= m_bits ? 4u : 3u;
+    return k < J ? k : J;
+}
+
 // Views of the workspace carved on the host.
 struct Work {
     TDesc *td;
@@ -255,6 +295,7 @@ struct Work {
     uint32_t ntensors;
     uint32_t ntiles_total;    // sum of ntiles
     bool shared;              // the probe pass's runs take several tensors
+    bool single;              // every filter is tested one hash at a time
     uint64_t slots;           // padded elements = ntiles_total * TILE
     uint64_t *pstat;          // probe pass look-back: per block (flag << 62 | trailing count), zeroed at set-up
     uint32_t *tcnt;           // per-tile counts of the current ordered pass

@@ -28,8 +28,8 @@ def emulator(tmp_path_factory):
         pytest.skip("g++ not found")
     d = tmp_path_factory.mktemp("probe_emu")
     src = open(os.path.join(CSRC, "bloom.hip")).read()
-    (d / "ext_sizes.inc").write_text(_between(src, "constexpr uint32_t QWAVE", "// The filter a tile is probed"))
-    (d / "ext_groups.inc").write_text(_between(src, "// Hashes per group", "// The receiver's dense output starts"))
+    (d / "ext_sizes.inc").write_text(_between(src, "constexpr uint32_t PB_THREADS", "// The filter a tile is probed"))
+    (d / "ext_groups.inc").write_text(_between(src, "// A tensor's filter as the probe", "// The receiver's dense output starts"))
     (d / "ext_windows.inc").write_text(_between(src, "// One window: the indices", "// A wave's window: ns steps"))
     exe = d / "probe_emu"
     cmd = [gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
