@@ -272,10 +272,9 @@ constexpr uint32_t FC_WORDS = 35072;  // filter words kept in LDS (137 KiB)
 // held: 284 and 294; 24 x 15 M: 1399 and 1258).  A filter that LDS holds whole
 // needs no memory read, and two hashes per group keep the lanes of a step busy,
 // whatever the members (12 K of 20 K elements: 54 and 49), but not for a tensor
-// of a single step (three of 100
-// elements: 24.8 and 26.8).
-__host__ __device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout, uint32_t d,
-                                                 uint32_t steps) {
+// of a single step (three of 100 elements: 24.8 and 26.8).
+__host__ __device__ __forceinline__ uint32_t probe_hashes(uint32_t m_bits, uint32_t k, uint32_t lim, uint32_t layout,
+                                                          uint32_t d, uint32_t steps) {
     const bool part = layout == LAYOUT_PARTITIONED;
     if (lim >= m_bits && !part) return d > QWAVE ? (k > 1 ? 2u : 1u) : 0u;
     // an m-bit filter of k hashes has about m ln 2 / k members
